@@ -46,7 +46,7 @@ struct GdnArgs {
     float *drift_zero;      // the caller's drift_partials (either layout) or null
     int drift_zero_per_frame;  // pairs per frame in it: H_v, or H_v * n_split for per-slice pairs
     int prep_per_vhead;     // prep grid (tiles, H_v) instead of (tiles, H_k)
-    // whole-head kernel: 0 one launch; 1, 2 the whole-head and the half-head
+    // whole-head kernel: 0 one launch (of whole or of half heads); 1, 2 the whole-head and the half-head
     // launch of a call split at a frame boundary (from which at most
     // wide_tail_streams streams have tiles left)
     int wide_phase, wide_tail_streams;
@@ -220,7 +220,7 @@ __device__ __forceinline__ float row_sq_sum16(half8 ef, int ln) {
 
 // Sequential kernel owning all d_v rows of a (stream, v-head) per workgroup
 // (gdn_wide.hip); returns the launch error.
-hipError_t launch_gdn_wide(const GdnArgs &a, int n_heads, int tail_streams, bool o_bf16, bool drift,
+hipError_t launch_gdn_wide(const GdnArgs &a, int n_heads, int cus, bool o_bf16, bool drift,
                            hipStream_t stream);
 
 }  // namespace ds

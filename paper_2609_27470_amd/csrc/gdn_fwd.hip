@@ -1093,11 +1093,17 @@ __global__ __launch_bounds__(256) void gdn_write_finalize_kernel(const float *ws
 // ============================================================================
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// The sequential part runs one workgroup per (stream, v-head) (gdn_wide.hip)
-// when there are enough heads to fill the GPU that way; otherwise one
-// workgroup per 16-row slice of a head (8 per head at d = 128), which is what
-// fills it for a single stream.
-constexpr int WIDE_MIN_HEADS = 256;
+// The sequential part runs one or two workgroups per (stream, v-head)
+// (gdn_wide.hip) from WIDE_MIN_HEADS heads on; below, one workgroup per 16-row
+// slice of a head (8 per head at d = 128).  The slices fill the GPU from 32
+// heads, but each of them loads the whole tile, so from there on their time
+// grows with the heads (8192 tokens per stream of 32 heads: 186, 352, 480, 627,
+// 1092 us a call with 1, 2, 3, 4, 7 streams); half or whole heads load it two
+// times or once, and their time grows only once the CUs are full (310, 335, 378,
+// 415, 578 us).  At 64 heads they are level or ahead (8191 tokens x 8 streams of
+// 8 heads 392 -> 363 us, 1024 tokens x 2 of 32 58 -> 57, 100 tokens x 2 of 32
+// 24 -> 22), at 72 ahead everywhere (4096 tokens 268 -> 194, 128 tokens 32 -> 24).
+constexpr int WIDE_MIN_HEADS = 64;
 static bool use_wide(int B, int H_v, int d) { return d == 128 && (long long)B * H_v >= WIDE_MIN_HEADS; }
 
 // compute units of the current device (looked up once per device)
@@ -1159,7 +1165,9 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     a.snapshots = p.snapshots;
     a.wsT = p.wsT;
     a.wsP = p.wsP;
-    a.wsQ = use_wide(p.B, p.H_v, D) ? nullptr : p.wsQ;
+    // (a call without tokens takes the per-slice kernel, which only copies the state)
+    const bool wide = D == 128 && use_wide(p.B, p.H_v, D) && p.tiles_max > 0;
+    a.wsQ = wide ? nullptr : p.wsQ;
     a.wsGam = p.wsGam;
     a.wsWrite = p.write_partials ? p.wsWrite : nullptr;
     a.wsStart = p.wsStart;
@@ -1188,12 +1196,12 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     // or a third group of waves, costs what the launch saves.)  Not with the
     // per-head drift sums, whose slice counters the prep pass clears before any
     // sequential workgroup runs.
-    const bool one_launch = !use_wide(p.B, p.H_v, D) && p.tiles_max > 0 && p.tiles_max <= 2 && !fused_drift;
+    const bool one_launch = !wide && p.tiles_max > 0 && p.tiles_max <= 2 && !fused_drift;
     if (p.tiles_max > 0 && !one_launch) {
         // tiles rounded up to a multiple of 8 (workgroups past the last tile exit)
         const long long n_prep = (long long)((p.tiles_max + 7) / 8) * 8 * (a.prep_per_vhead ? p.H_v : p.H_k);
         // the whole-head kernel forms P itself (prep without q, K Q^T and P)
-        if (D == 128 && use_wide(p.B, p.H_v, D))
+        if (wide)
             hipLaunchKernelGGL((gdn_prep_kernel<D, false>), dim3((unsigned)n_prep), dim3(256), 0, stream, a);
         else
             hipLaunchKernelGGL((gdn_prep_kernel<D, true>), dim3((unsigned)n_prep), dim3(256), 0, stream, a);
@@ -1202,11 +1210,8 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     }
     // the frame-end work is compiled out when neither drift sums nor snapshots are asked for
     const bool drift = p.drift_partials || p.snapshots;
-    if (D == 128 && use_wide(p.B, p.H_v, D)) {
-        // whole heads: per-head drift pairs are added by the workgroup itself
-        // the tail of the longest streams as half heads when at most as many
-        // streams as fill the GPU that way are left
-        hipError_t e = launch_gdn_wide(a, p.B * p.H_v, device_cus() / (2 * p.H_v), p.o_bf16, drift, stream);
+    if (wide) {
+        hipError_t e = launch_gdn_wide(a, p.B * p.H_v, device_cus(), p.o_bf16, drift, stream);
         if (e != hipSuccess) return e;
         if (p.write_partials && p.n_frames > 0) {
             hipLaunchKernelGGL(gdn_write_finalize_kernel, dim3(p.n_frames, p.H_v), dim3(256), 0, stream, p.wsWrite,

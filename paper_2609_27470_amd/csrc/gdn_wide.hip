@@ -36,7 +36,8 @@
 // two launches: whole heads up to the cut (the first frame boundary from
 // which at most as many streams are left as fill the GPU with two
 // workgroups per head), then half heads (NSL = 1: 64 rows per workgroup, one
-// 16-row slice per compute wave) from the states the first launch wrote.  A
+// 16-row slice per compute wave) from the states the first launch wrote.  Calls
+// whose heads fill at most half the CUs run as half heads throughout.  A
 // half head's drift sums go out per slice; with per-head pairs the second of
 // a head's two workgroups to finish adds the 8 slices in order.
 #include <type_traits>
@@ -770,16 +771,20 @@ static hipError_t launch_wide_nsl(const GdnArgs &a, int n_wg, bool o_bf16, bool 
     return hipGetLastError();
 }
 
-// One launch of whole heads, or, for calls whose frames are whole tiles and
-// when at most tail_streams streams fit the GPU as half heads, whole heads up
+// Half heads throughout, in one launch, when two workgroups per head do not
+// outnumber the compute units (4 streams of 6151, 4097, 8190 and 5333 tokens
+// with 32 heads: 467 us a call on the per-slice kernel, 368 here).  Otherwise
+// one launch of whole heads, or, for calls whose frames are whole tiles and
+// when at most tail_streams streams fill the GPU as half heads, whole heads up
 // to the cut (the tile from which at most tail_streams streams are left,
 // on a frame boundary) and half heads from it, the second launch starting
 // from the states the first one wrote.
-hipError_t launch_gdn_wide(const GdnArgs &a0, int n_heads, int tail_streams, bool o_bf16, bool drift,
-                           hipStream_t stream) {
+hipError_t launch_gdn_wide(const GdnArgs &a0, int n_heads, int cus, bool o_bf16, bool drift, hipStream_t stream) {
     GdnArgs a = a0;
-    const bool split = tail_streams >= 1 && a.frame_len > 0 && a.frame_len % TILE == 0;
-    a.wide_tail_streams = tail_streams;
+    a.wide_tail_streams = cus / (2 * a.H_v);
+    a.wide_phase = 0;
+    if (2 * n_heads <= cus) return launch_wide_nsl<1>(a, 2 * n_heads, o_bf16, drift, stream);
+    const bool split = a.wide_tail_streams >= 1 && a.frame_len > 0 && a.frame_len % TILE == 0;
     a.wide_phase = split ? 1 : 0;
     hipError_t e = launch_wide_nsl<2>(a, n_heads, o_bf16, drift, stream);
     if (e != hipSuccess || !split) return e;

@@ -1,5 +1,5 @@
 """The whole-head sequential kernel (one workgroup per (stream, v-head), used
-when B * H_v reaches 256 at d = 128) against the fp64 oracle (Section 3.2,
+from B * H_v = 64 at d = 128; as half heads up to half as many heads as CUs) against the fp64 oracle (Section 3.2,
 Eq. 2 and Eq. 3), on batches of many short streams that select it: ragged,
 empty and one-token streams, a non-zero entry state, snapshots, every drift
 aggregation, per-slice drift pairs, bf16 o and the write signal; frame
@@ -194,3 +194,42 @@ def test_wide_state_in_place(ds):
     assert np.array_equal(a["o"], b["o"])
     assert np.array_equal(a["S"], b["S"])
     assert np.array_equal(a["partials"], b["partials"])
+
+
+@pytest.mark.parametrize("B,H_k,H_v,frame_len", [(15, 2, 4, 128), (16, 2, 4, 128), (16, 4, 4, 0), (8, 4, 16, 64),
+                                                 (33, 2, 4, 128), (43, 3, 6, 0)])
+def test_dispatch_edges_against_oracle(ds, B, H_k, H_v, frame_len):
+    """Both sides of the line between the per-slice kernel and half heads (60 and
+    64 heads) and of the line between half and whole heads (128 and 132 heads on
+    256 CUs; 258): ragged streams, the state in place, per-slice pairs that add up
+    to the per-head ones, the write signal."""
+    x = _batch(B, 11, hi=200, frame_len=frame_len, H_k=H_k, H_v=H_v)
+    S0 = (np.random.default_rng(3).standard_normal((B, H_v, 128, 128)) * 0.1).astype(np.float32).astype(np.float64)
+    gpu = run_gpu(ds, x, state_in=S0, in_place=True)
+    ref = oracle.gdn_forward(x.q, x.k, x.v, x.g, x.beta, x.cu_seqlens, frame_len, S0=S0)
+    _check(ds, gpu, ref)
+    args = [dev_bf16(x.q), dev_bf16(x.k), dev_bf16(x.v), dev_f32(x.g), dev_f32(x.beta), lengths_of(x), frame_len]
+    r = ds.gdn_chunk_fwd(*args, state_in=dev_f32(S0), drift_per_slice=True, write_partials=True)
+    ps = r["drift_partials"].cpu().numpy().reshape(-1, H_v, 8, 2)
+    tot = ps[:, :, 0].copy()
+    for s in range(1, 8):
+        tot = tot + ps[:, :, s]
+    assert np.array_equal(tot, gpu["partials"].astype(np.float32))
+    assert np.array_equal(r["o"].cpu().numpy(), gpu["o"].astype(np.float32))
+
+
+@pytest.mark.parametrize("B", [15, 16, 64])
+def test_no_tokens(ds, B):
+    """A call without tokens passes the states through and zeroes the frames' pairs, whichever kernel its heads select."""
+    shp = ds.gdn_shape([0] * B, 2, 4, 128, 0)
+    shp.n_frames = 2
+    S0 = torch.randn(B, 4, 128, 128, device=DEV)
+    S1, dp = torch.empty_like(S0), torch.full((2, 4, 2), float("nan"), device=DEV)
+    ws = torch.empty(max(ds.gdn_workspace_bytes(shp), 1), dtype=torch.uint8, device=DEV)
+    cu = torch.zeros(B + 1, dtype=torch.int32, device=DEV)
+    import ctypes
+    P = lambda t: ctypes.c_void_p(t.data_ptr())
+    rc = ds.lib().gdn_chunk_fwd(ctypes.byref(shp), None, None, None, None, None, P(cu), P(S0), P(S1), None, 1, 1.0, P(dp),
+                                None, None, P(ws), ws.numel(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(S0, S1) and torch.all(dp == 0.0)
