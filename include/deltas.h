@@ -271,9 +271,8 @@ ds_status kv_evict_topk(const ds_kv_shape *shape, void *const *k_layers, void *c
  *   0  ok;
  *   1  the cache invariants were found broken: nothing was moved or rewritten;
  *   2  the kept count differed from M (an internal check): nothing was moved;
- *   3  kv_evict_topk only: a bounded wait of the in-place gather timed out;
- *      every move stopped at once, so K/V rows, pos and chunk_id in [0, M)
- *      are partially compacted and unspecified.
+ *   3  reserved (a wait of the in-place move that timed out; the move no
+ *      longer waits on anything).
  * The calls return DS_OK before their kernels run, so a failure shows only
  * here: read the word after synchronising, or fold it into a device-side
  * maximum after each call to check many events with one read.  The two

@@ -314,9 +314,9 @@ def kv_evict_topk_indexed_noalloc(pos, chunk_id, slot, chunk_scores, length, M, 
 
 
 def kv_device_status(workspace):
-    """(outcome, moves-stopped flag, wait-timeout flag) left by the last eviction
+    """(outcome, moves-skipped flag, 0) left by the last eviction
     that ran on this workspace (synchronises).  Outcome: 0 ok, 1 cache
-    invariants broken, 2 keep count wrong, 3 gather wait timed out."""
+    invariants broken, 2 keep count wrong."""
     return workspace[:12].view(torch.int32).cpu().tolist()
 
 

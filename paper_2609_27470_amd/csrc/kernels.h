@@ -67,12 +67,11 @@ hipError_t launch_drift(const float *partials, int L, int F, int H_v, int mode, 
 constexpr int KV_MAX_PLANES = 64;  // 2 * n_layers
 
 struct KvWorkspace {
-    size_t offStatus, offPlanes, offKeep, offInv, offThRun, offRunStart, offRunKey, offRunBkt, offRunTake,
-        offRunFrom, offFlags, offStage, offStageMeta, total;
-    int n_chunks;    // 64 KiB pieces of one token's rows over all layers
-    int stage_rows;  // destinations per staged block
+    size_t offStatus, offPlanes, offKeep, offThRun, offRunStart, offRunKey, offRunBkt, offRunTake, offRunFrom,
+        offStage, total;
+    size_t stage_bytes;  // staging area of the moves
 };
-// n_layers = 0: the indexed variant's workspace (no gather flags)
+// n_layers = 0: the indexed variant's workspace (no staging area)
 KvWorkspace kv_workspace_layout(int n_layers, int row_bytes, int capacity);
 
 struct KvLaunch {
@@ -82,7 +81,7 @@ struct KvLaunch {
     const float *chunk_scores;
     int num_chunks, len, M, n_sink, n_window, n_buckets;
     int32_t *keep_out;
-    int32_t *slot, *free_out;  // indexed variant (slot != NULL): no K/V planes, no gather
+    int32_t *slot, *free_out;  // indexed variant (slot != NULL): no K/V planes, no moves
     int32_t *outcome_out;      // indexed variant: device copy of the outcome word, or NULL
     char *ws;
     KvWorkspace lay;

@@ -12,7 +12,7 @@
 //     newest tokens first (ties within a chunk go to the newer position);
 //   * the leftover budget is filled the same way over all spans from the
 //     tokens not yet kept;
-//   * kept slots -> ascending keep list and its inverse on [0, M).
+//   * kept slots -> ascending keep list.
 // Slot data is read in blocks of 4 consecutive slots per thread with one
 // 16-byte load (adjacent lanes read adjacent 16 bytes), 4 Ki slots per
 // block and memory round trip.
@@ -20,20 +20,18 @@
 // select kernel itself compacts pos, chunk_id and slot (the physical row of
 // each logical token) in place and lists the freed physical rows.
 // The kept rows then move down in place: slot d receives row keep[d]
-// (keep[d] >= d); the shift keep[d] - d never decreases with d.
-// kv_gather handles the destinations whose shift is large.  Writing slot d is
-// safe once the reader of row d -- the destination inv[d] < d, if row d is
-// kept -- has its data in registers.  Workgroups take increasing tickets,
-// signal "read done" before they wait, and only ever wait on lower tickets,
-// so every wait ends; the wait is also bounded and reports a timeout in the
-// status word instead of hanging.  Its parallelism is the shift itself (only
-// rows a shift apart are independent), so destinations with a small shift
-// (fewer than STAGE_BYTES of rows) go first through kv_stage instead: blocks
-// of destinations are copied to a staging area and back in two launches,
-// with no waits at all (a block only reads at or above its own start, and
-// the blocks run in order).
+// (keep[d] >= d); the shift keep[d] - d never decreases with d.  kv_slide cuts
+// every plane into column strips of at most 128 bytes per row.  One wave walks a
+// strip's destinations in ascending order, reading a batch of source rows ahead
+// of the one it writes: no row is read by a later destination than its own, so
+// within a strip the order alone makes the move safe, and strips share no byte:
+// no waits, no flags, every byte read and written once.  Where the strips are
+// too few to fill the GPU, the destinations are also cut into segments; the
+// rows that a segment reads from behind its own end (at most len - M) are copied
+// to a staging area first (kv_stage_tails), before any segment writes.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -44,11 +42,7 @@ constexpr int SEL_THREADS = 1024;
 constexpr int SEL_PER = 4;                          // consecutive slots per thread per pass block
 constexpr int SEL_BLOCK = SEL_THREADS * SEL_PER;
 static_assert(SEL_PER == 4, "pass 2 stores a thread's four inverse entries as one int4");
-constexpr int GATHER_U = 16;                        // uint4 per thread per group
-constexpr int SPIN_LIMIT = 1 << 22;
-constexpr long long STAGE_BYTES = 64ll << 20;       // below this much shift, rows are staged
-constexpr long long STAGE_AREA = 256ll << 20;       // staging area of one block of destinations
-constexpr int STAGE_WG = 1024;                      // workgroups per staging launch (each loops over rows)
+constexpr long long STAGE_AREA = 256ll << 20;       // at most this much staging area for the segments' tails
 
 // pointer into global memory (lets the compiler emit global rather than flat accesses)
 #define GPTR(T) __attribute__((address_space(1))) T *
@@ -59,20 +53,15 @@ struct KvArgs {
     int32_t *chunk;
     const float *scores;
     int num_chunks, len, M, n_s, n_w, N;
-    int n_flags, n_chunks;
-    int stage_shift;   // destinations with keep[d] - d below this are staged
-    int32_t *status;   // [0] outcome (0 ok, 1 invariants broken, 2 keep count wrong, 3 gather wait timed
-                       // out), [1] skip or stop the moves, [2] wait timed out, [3] first moved slot,
-                       // [4] first slot moved by the ticket gather (the staged ones lie in [3], [4])
-    uint32_t *ticket;
-    int32_t *keep, *inv, *run_start, *run_bkt, *run_take, *run_from, *th_run;
+    int32_t *status;   // [0] outcome (0 ok, 1 invariants broken, 2 keep count wrong), [1] skip the moves,
+                       // [3] first moved slot
+    int32_t *keep, *run_start, *run_bkt, *run_take, *run_from, *th_run;
     unsigned long long *run_key;
-    int32_t *flags;
     int32_t *keep_out;
     int32_t *slot;      // indexed variant: physical row of each logical token (NULL: gather variant)
     int32_t *free_out;  // indexed variant: physical rows of the evicted tokens
     int32_t *outcome_out;  // indexed variant: a copy of status[0] for the caller (or NULL)
-    char **plane_tab;  // device copy of the plane pointers, read by the gather
+    char **plane_tab;  // device copy of the plane pointers, read by the moves
     char *planes[KV_MAX_PLANES];
     int n_planes;
 };
@@ -211,7 +200,6 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         a.status[0] = 0;
         a.status[1] = 0;
         a.status[2] = 0;
-        *a.ticket = 0u;
         s_bad = 0;
     }
     // copy of the plane table with constant indices (no dynamic indexing of
@@ -471,10 +459,9 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
     __syncthreads();
     auto run_from = [&](int r) { return in_lds ? s_from[r] : a.run_from[r]; };
 
-    // ---- pass 2: keep list (ascending) and its inverse on destinations [0, M)
+    // ---- pass 2: keep list (ascending)
     int total_kept = 0;
     int first_move = a.M;  // smallest destination d with keep[d] != d
-    int split = a.M;       // smallest destination d with keep[d] - d >= stage_shift
     const int n_evict = a.len - a.M;
     // the next block's entries are loaded while this one is processed
     int n2ch[SEL_PER], n2sl[SEL_PER], n2pc = -1, n2r = -1;
@@ -516,37 +503,26 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
             }
         }
         // the block's keep entries and freed slots are collected in LDS and
-        // leave as contiguous stores; the inverse leaves as one 16-byte store
-        // per thread (scattered 4-byte stores would load the memory pipeline)
+        // leave as contiguous stores (scattered 4-byte stores would load the
+        // memory pipeline)
         int tot = 0;
         int off = total_kept + block_excl_scan(__popc(mask), s_scan, tot);
         const int ev_base = base - total_kept;  // tokens evicted before this block
-        int invv[SEL_PER];
 #pragma unroll
         for (int k = 0; k < SEL_PER; ++k) {
             const int i = lo + k;
-            invv[k] = -1;
             if (i < a.len) {
                 if (mask & (1u << k)) {
                     if (off < a.M) {
                         s_keep[off - total_kept] = i;
                         if (off != i) first_move = min(first_move, off);
-                        if (i - off >= a.stage_shift) split = min(split, off);
                     }
-                    invv[k] = off;
                     ++off;
                 } else if (a.slot) {
                     // evicted token i is the (i - off)-th evicted one in logical order
                     s_free[i - off - ev_base] = sl[k];
                 }
             }
-        }
-        if (lo + SEL_PER <= a.M) {
-            *(int4 *)(a.inv + lo) = int4{invv[0], invv[1], invv[2], invv[3]};
-        } else {
-#pragma unroll
-            for (int k = 0; k < SEL_PER; ++k)
-                if (lo + k < a.M) a.inv[lo + k] = invv[k];
         }
         lds_sync();
         const int kn = min(tot, a.M - total_kept);
@@ -562,31 +538,20 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         total_kept += tot;
     }
     // ---- moving destinations form the suffix [first_move, M) (keep[d] - d is
-    // nondecreasing); clear their flags for the gather
+    // nondecreasing)
     {
         // minimum over the block: within each wave by lane exchanges, then over
         // the 16 wave results (one LDS atomic per thread would serialize)
-        __shared__ int s_first[SEL_THREADS / 64], s_split[SEL_THREADS / 64];
+        __shared__ int s_first[SEL_THREADS / 64];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            first_move = min(first_move, __shfl_xor(first_move, off, 64));
-            split = min(split, __shfl_xor(split, off, 64));
-        }
-        if ((tid & 63) == 0) {
-            s_first[tid >> 6] = first_move;
-            s_split[tid >> 6] = split;
-        }
+        for (int off = 32; off > 0; off >>= 1) first_move = min(first_move, __shfl_xor(first_move, off, 64));
+        if ((tid & 63) == 0) s_first[tid >> 6] = first_move;
         lds_sync();
 #pragma unroll
-        for (int w = 0; w < SEL_THREADS / 64; ++w) {
-            first_move = min(first_move, s_first[w]);
-            split = min(split, s_split[w]);
-        }
-        split = max(split, first_move);
+        for (int w = 0; w < SEL_THREADS / 64; ++w) first_move = min(first_move, s_first[w]);
     }
     if (tid == 0) {
         a.status[3] = first_move;
-        a.status[4] = split;
         const bool count_ok = total_kept == a.M;
         if (!count_ok) {  // cannot happen for valid arguments; never move data then
             a.status[0] = 2;
@@ -594,15 +559,6 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         }
         if (a.outcome_out) *a.outcome_out = count_ok ? 0 : 2;
     }
-    {
-        // flags of the moving destinations back to zero, 16 bytes per store
-        const int fs = first_move * a.n_chunks, fe = a.n_flags;
-        const int fa = min((fs + 3) & ~3, fe), fb = max(fa, fe & ~3);
-        if (tid < fa - fs) a.flags[fs + tid] = 0;
-        for (int q = fa / 4 + tid; q < fb / 4; q += SEL_THREADS) ((int4 *)a.flags)[q] = int4{0, 0, 0, 0};
-        if (tid < fe - fb) a.flags[fb + tid] = 0;
-    }
-
     // ---- indexed variant: pos, chunk_id and slot move down in place,
     // new[d] = old[keep[d]] for the moving destinations [first_move, M).
     // keep[d] >= d, so a block of destinations only reads at or above its own
@@ -651,234 +607,190 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
     }
 }
 
-struct GatherArgs {
+struct SlideArgs {
     char *const *plane_tab;
     uint32_t row_bytes, row_units;  // bytes and 16-byte units of one plane row
-    int n_planes, planes_per_group;
-    int M, n_chunks;
-    int32_t *pos, *chunk;
-    const int32_t *keep, *inv;
-    int32_t *flags, *status;
-    uint32_t *ticket;
-    char *trash;  // 8 KiB that stores with nothing to write go to (the staging area, idle by then)
-};
-
-// s_waitcnt immediate that waits until at most n vector memory operations of
-// this wave are in flight (lgkm and exp counters not waited for)
-constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
-
-// Moving destinations [first, M) are handed out in ticket order, ROWS
-// consecutive slots per ticket; for each slot and each group of planes the
-// workgroup reads the source rows, signals, waits for the reader of the slot
-// and writes.  KPR = 16-byte units per thread per plane row
-// (row_bytes <= 4096 KPR); a plane group holds 16 / KPR plane rows.
-constexpr int GATHER_ROWS = 8;
-// workgroups of the gather, each taking tickets until none is left: three for
-// every four CUs of MI355X moved a 1 GiB eviction fastest (fewer streams of
-// copies in flight than one per CU, which also beat one per ticket)
-constexpr int GATHER_WG = 192;
-
-template <int KPR>
-__global__ __launch_bounds__(256) void kv_gather_kernel(GatherArgs a) {
-    constexpr int PPG = GATHER_U / KPR;
-    __shared__ int s_t;
-    __shared__ int s_src[GATHER_ROWS], s_dep[GATHER_ROWS];
-    __shared__ char *s_pt[KV_MAX_PLANES];
-    if (a.status[1]) return;
-    const int first = a.status[4];
-    const int n_work = (a.M - first + GATHER_ROWS - 1) / GATHER_ROWS;
-    if ((int)blockIdx.x >= n_work) return;  // more workgroups than moving rows: take no ticket
-    const int tid = threadIdx.x;
-    if (tid < a.n_planes) s_pt[tid] = a.plane_tab[tid];
-    // tickets are taken until none is left, so the grid drains evenly; a
-    // workgroup only waits for slots of lower tickets, which running
-    // workgroups hold
-    __shared__ int s_stop;
-    for (;;) {
-        if (tid == 0) {
-            s_t = (int)atomicAdd(a.ticket, 1u);
-            // a workgroup whose wait timed out stopped every move: take no more work
-            s_stop = __hip_atomic_load(&a.status[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        if (s_t >= n_work || s_stop) break;
-        const int d_lo = first + s_t * GATHER_ROWS;
-        const int d_hi = min(d_lo + GATHER_ROWS, a.M);
-        // sources and readers of the ticket's slots, in LDS: a global load inside
-        // the pipeline below would make the compiler wait for every load in flight
-        if (tid < d_hi - d_lo) {
-            s_src[tid] = a.keep[d_lo + tid];
-            s_dep[tid] = a.inv[d_lo + tid];  // destination whose source is row d (-1 if row d is evicted)
-        }
-        __syncthreads();
-
-        // Units u = (slot d_lo + u / n_chunks, plane group u % n_chunks) in two
-        // register buffers.  Per unit: wait for its loads, signal that its source
-        // rows are held, wait for the reader of its slot, issue the next unit's
-        // loads, write the slot -- so a workgroup's writes overlap its next reads.
-        // Each unit issues exactly LPU loads and LPU stores per lane (lanes with
-        // nothing to store write to the trash area) so that the wait can count them
-        // (vmcnt counts loads and stores together, in issue order); plane pointers
-        // and slot metadata come from LDS, since a global load whose value is used
-        // at once would make the compiler wait for every load in flight.
-        constexpr int LPU = GATHER_U + 2;
-        const int n_units = (d_hi - d_lo) * a.n_chunks;
-        u32x4 bufA[GATHER_U], bufB[GATHER_U];
-        int pvA = 0, cvA = 0, pvB = 0, cvB = 0;
-        auto load = [&](int u, u32x4 (&buf)[GATHER_U], int &pv, int &cv) __attribute__((always_inline)) {
-            const int c = u % a.n_chunks;
-            const int src = s_src[u / a.n_chunks];
-            const int p0 = c * a.planes_per_group;
-            // (units past the row or planes past the group re-read a valid address)
-    #pragma clang loop unroll(full)
-            for (int pi = 0; pi < PPG; ++pi) {
-                const int p = min(p0 + pi, a.n_planes - 1);
-                GPTR(const char) row = (GPTR(const char))s_pt[p] + (size_t)src * a.row_bytes;
-    #pragma clang loop unroll(full)
-                for (int k = 0; k < KPR; ++k) {
-                    const uint32_t unit = min((uint32_t)(tid + 256 * k), a.row_units - 1);
-                    buf[pi * KPR + k] = *(GPTR(const u32x4))(row + 16u * unit);
-                }
-            }
-            pv = a.pos[src];  // position and chunk id of the source row (lane 0 of group 0 stores them)
-            cv = a.chunk[src];
-        };
-        auto step = [&](int u, const u32x4 (&buf)[GATHER_U], int pv, int cv, u32x4 (&nbuf)[GATHER_U], int &npv, int &ncv)
-            __attribute__((always_inline)) {
-            const int d = d_lo + u / a.n_chunks, c = u % a.n_chunks;
-            const int dep = s_dep[u / a.n_chunks];
-            // this unit's loads: after them only the previous unit's stores were issued
-            if (u == 0)
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-            else
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm(LPU));
-            lds_sync();  // every lane holds this unit's source rows
-            if (tid == 0) {
-                __hip_atomic_store(&a.flags[d * a.n_chunks + c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                // ---- wait until the reader of row d (a lower slot, hence an
-                // earlier ticket or an earlier unit here) holds its data.  The
-                // wait is bounded: on a timeout every move stops (status[1]) and
-                // the call's outcome becomes 3; a workgroup that sees the stop
-                // while waiting leaves as well, without writing
-                if (dep >= first && dep != d) {  // readers below `first` were staged earlier
-                    int it = 0;
-                    const int ft = dep * a.n_chunks + c;
-                    while (__hip_atomic_load(&a.flags[ft], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
-                        if (++it >= SPIN_LIMIT) {
-                            __hip_atomic_store(&a.status[2], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            __hip_atomic_store(&a.status[0], 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            __hip_atomic_store(&a.status[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            s_stop = 1;
-                            break;
-                        }
-                        if ((it & 63) == 0 &&
-                            __hip_atomic_load(&a.status[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                            s_stop = 1;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(2);
-                    }
-                }
-            }
-            lds_sync();
-            if (s_stop) return false;
-            load(min(u + 1, n_units - 1), nbuf, npv, ncv);  // unconditional (a repeat past the end is never written)
-            // ---- write slot d
-            const int p0 = c * a.planes_per_group;
-            GPTR(u32x4) trash = (GPTR(u32x4))a.trash + tid;
-    #pragma clang loop unroll(full)
-            for (int pi = 0; pi < PPG; ++pi) {
-                const int p = p0 + pi;
-                const bool plane_ok = pi < a.planes_per_group && p < a.n_planes;
-                GPTR(char) row = (GPTR(char))s_pt[min(p, a.n_planes - 1)] + (size_t)d * a.row_bytes;
-    #pragma clang loop unroll(full)
-                for (int k = 0; k < KPR; ++k) {
-                    const uint32_t unit = (uint32_t)(tid + 256 * k);
-                    GPTR(u32x4) dst = (plane_ok && unit < a.row_units) ? (GPTR(u32x4))(row + 16u * unit) : trash;
-                    __builtin_nontemporal_store(buf[pi * KPR + k], dst);  // streaming: 230 -> 218 us on a 1 GiB event
-                }
-            }
-            const bool meta = c == 0 && tid == 0;
-            int32_t *tr = (int32_t *)(a.trash + 4096) + 2 * tid;
-            *(meta ? a.pos + d : tr) = pv;
-            *(meta ? a.chunk + d : tr + 1) = cv;
-            return true;
-        };
-        load(0, bufA, pvA, cvA);
-        for (int u = 0; u < n_units; u += 2) {
-            if (!step(u, bufA, pvA, cvA, bufB, pvB, cvB)) return;  // moves stopped (s_stop is workgroup-uniform)
-            if (u + 1 < n_units && !step(u + 1, bufB, pvB, cvB, bufA, pvA, cvA)) return;
-        }
-        __syncthreads();  // every lane is done with this ticket's LDS entries
-    }
-}
-
-struct StageArgs {
-    char *const *plane_tab;
-    uint32_t row_bytes, row_units;
-    int n_planes, planes_per_group, n_chunks;
-    int rows, block;  // destinations [block * rows, (block + 1) * rows)
+    int n_planes, strips;           // strips per plane
+    int M, n_evict, segments;
+    int seg_tail;                   // staged rows kept per segment, at most
     int32_t *pos, *chunk;
     const int32_t *keep, *status;
-    char *area;       // [rows][n_chunks][256 threads][16 units] 16-byte units
-    int32_t *meta;    // [rows][2] positions and chunk ids
+    char *area;  // [segments - 1][seg_tail][n_planes][row_bytes]
 };
 
-template <int KPR, bool READ>
-__device__ __forceinline__ void kv_stage_row(const StageArgs &a, int r, int c) {
-    constexpr int PPG = GATHER_U / KPR;
-    const int tid = threadIdx.x;
-    const int d = a.block * a.rows + r;
-    GPTR(u32x4) slot = (GPTR(u32x4))(a.area + ((size_t)r * a.n_chunks + c) * (size_t)(GATHER_U * 16 * 256));
-    const int row = READ ? a.keep[d] : d;
-    const int p0 = c * a.planes_per_group;
-#pragma clang loop unroll(full)
-    for (int pi = 0; pi < PPG; ++pi) {
-        const int p = p0 + pi;
-        if (pi >= a.planes_per_group || p >= a.n_planes) break;
-        GPTR(char) base = (GPTR(char))a.plane_tab[p] + (size_t)row * a.row_bytes;
-#pragma clang loop unroll(full)
-        for (int k = 0; k < KPR; ++k) {
-            const uint32_t unit = (uint32_t)(tid + 256 * k);
-            if (unit < a.row_units) {
-                GPTR(u32x4) g = (GPTR(u32x4))(base + 16u * unit);
-                GPTR(u32x4) t = slot + (pi * KPR + k) * 256 + tid;
-                // nontemporal stores, as in the ticket gather (streamed chunks ~1 % faster)
-                if (READ) __builtin_nontemporal_store(*g, t); else __builtin_nontemporal_store(*t, g);
-            }
-        }
-    }
-    if (c == 0 && tid == 0) {
-        if (READ) {
-            a.meta[2 * r] = a.pos[row];
-            a.meta[2 * r + 1] = a.chunk[row];
-        } else {
-            a.pos[d] = a.meta[2 * r];
-            a.chunk[d] = a.meta[2 * r + 1];
-        }
-    }
+// First destination of segment s (the moving destinations [first, M) in equal parts).
+__device__ __forceinline__ int seg_begin(const SlideArgs &a, int first, int s) {
+    return first + (int)((long long)(a.M - first) * s / a.segments);
 }
 
-// Workgroup x of plane group y handles destinations x, x + STAGE_WG, ... of
-// the block.  READ copies the source rows of the staged destinations into the
-// area, WRITE copies them to their slots.  Destinations outside
-// [status[3], status[4]) are skipped, so a launch with nothing to stage ends
-// at once.
-template <int KPR, bool READ>
-__global__ __launch_bounds__(256) void kv_stage_kernel(StageArgs a) {
+// The first destination in [0, M] whose source is slot x or later, by the 64
+// lanes of a wave together (three rounds for 256 Ki slots).
+__device__ __forceinline__ int first_from(const int32_t *keep, int M, int x, int lane) {
+    int lo = 0, hi = M;
+    while (lo < hi) {
+        const int step = (hi - lo + 63) / 64, i = lo + lane * step;
+        const int c = __popcll(__ballot(i < hi && keep[i] < x));  // lanes 0 .. c - 1 lie below
+        if (c == 0) break;
+        const int l = lo;
+        lo = l + (c - 1) * step + 1;
+        hi = min(hi, l + c * step);
+    }
+    return lo;
+}
+
+// The rows that segment blockIdx.y reads from behind its end, destination e0 +
+// blockIdx.x (of at most seg_tail), to the staging area.
+__global__ __launch_bounds__(256) void kv_stage_tails_kernel(SlideArgs a) {
     if (a.status[1]) return;
-    const int lo = max(a.status[3] - a.block * a.rows, 0);
-    const int hi = min(a.status[4] - a.block * a.rows, a.rows);
-    for (int r = lo + (int)blockIdx.x; r < hi; r += (int)gridDim.x) kv_stage_row<KPR, READ>(a, r, (int)blockIdx.y);
+    const int tid = threadIdx.x, s = blockIdx.y, first = a.status[3];
+    const int lo = seg_begin(a, first, s), hi = seg_begin(a, first, s + 1);
+    const int e0 = max(first_from(a.keep, a.M, hi, tid & 63), lo);
+    const int r = blockIdx.x, d = e0 + r;
+    if (d >= hi) return;
+    const size_t src = (size_t)a.keep[d] * a.row_bytes;
+    GPTR(u32x4) dst = (GPTR(u32x4))(a.area + ((size_t)s * a.seg_tail + r) * a.n_planes * a.row_bytes);
+    const uint32_t total = a.n_planes * a.row_units;
+    for (uint32_t u0 = tid; u0 < total; u0 += 256 * 4) {
+        u32x4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t u = min(u0 + 256 * k, total - 1), p = u / a.row_units;
+            v[k] = *(GPTR(const u32x4))(a.plane_tab[p] + src + 16u * (u - p * a.row_units));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (u0 + 256 * k < total) dst[u0 + 256 * k] = v[k];
+    }
 }
 
-// 16-byte units per thread per plane row, rounded up to a power of two.
-static int gather_kpr(int row_bytes) {
-    const int need = (row_bytes + 4095) / 4096;
-    int k = 1;
-    while (k < need) k *= 2;
-    return k;
+// Wave (segment, plane, strip): destinations of the segment in batches of
+// SLIDE_U loads per lane, 64 / LPR rows each; the next batch's rows are on
+// their way while the current one is written.  Workgroup 0 moves pos and chunk.
+//
+// Bound by HBM: 2 bytes of traffic per moved byte, against 4 through the
+// staging area that this replaces for small shifts, and no launches that end at
+// once, tickets or waits.  Whole evictions (ranking included), before -> now:
+// 16384 of 17408 tokens of 64 KiB, 14.5 k of them moved, 393 -> 390 us (5.2 TB/s);
+// one chunk of 125 by the paper's policy from 16384 tokens of 64 KiB 758 -> 382,
+// from 8192 of 64 KiB 436 -> 227, of 32 KiB 214 -> 81; from 16384 of 8 KiB
+// 195 -> 82; 8192 of 8704 tokens of 16 KiB 171 -> 73; half of 32768 tokens of
+// 64 KiB 455 -> 444.
+// A strip is 128 bytes, one cache line written by one instruction: 64-byte strips
+// (twice the waves) took 545 us on the first of these, 256-byte strips 484.
+// 12 loads in flight per lane: 8 took 432, 16 410, 32 408; 4 waves per
+// workgroup: 2 took 414, 8 734.
+constexpr int SLIDE_WAVES = 4;
+constexpr int SLIDE_U = 12;
+
+template <int LPR, bool NT>
+__global__ __launch_bounds__(64 * SLIDE_WAVES) void kv_slide_kernel(SlideArgs a) {
+    constexpr int R = 64 / LPR, N = R * SLIDE_U;  // rows per load, rows per batch
+    if (a.status[1]) return;
+    const int tid = threadIdx.x, lane = tid & 63, first = a.status[3];
+    if (blockIdx.x == 0) {
+        // positions and chunk ids, in blocks of destinations: everything read before
+        // anything is written, and later blocks only read behind what this one writes
+        constexpr int T = 64 * SLIDE_WAVES, PER = 16;
+        for (int b = first; b < a.M; b += T * PER) {
+            int vp[PER], vc[PER];
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int src = a.keep[min(b + T * k + tid, a.M - 1)];
+                vp[k] = a.pos[src];
+                vc[k] = a.chunk[src];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int d = b + T * k + tid;
+                if (d < a.M) {
+                    a.pos[d] = vp[k];
+                    a.chunk[d] = vc[k];
+                }
+            }
+            __syncthreads();
+        }
+        return;
+    }
+    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x - 1) * SLIDE_WAVES + (tid >> 6));
+    const int per_seg = a.n_planes * a.strips, s = w / per_seg;
+    if (s >= a.segments) return;
+    const int p = (w - s * per_seg) / a.strips, strip = w - s * per_seg - p * a.strips;
+    const int lo = seg_begin(a, first, s), hi = seg_begin(a, first, s + 1);
+    if (lo >= hi) return;
+    // destinations from e0 on read the staged copy of their row
+    const int e0 = s + 1 < a.segments ? max(first_from(a.keep, a.M, hi, lane), lo) : hi;
+    const uint32_t unit = (uint32_t)(strip * LPR + lane % LPR);
+    const bool mine = unit < a.row_units;  // the last strip of a row may be narrower
+    const int lr = lane / LPR;
+    GPTR(char) plane = (GPTR(char))a.plane_tab[p] + 16u * min(unit, a.row_units - 1);
+    GPTR(const char) staged = (GPTR(const char))a.area + 16u * min(unit, a.row_units - 1) +
+                              ((size_t)s * a.seg_tail * a.n_planes + p) * a.row_bytes;
+    const size_t staged_row = (size_t)a.n_planes * a.row_bytes;
+    auto load_idx = [&](int b, int(&ix)[SLIDE_U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < SLIDE_U; ++u) ix[u] = ((GPTR(const int32_t))a.keep)[min(b + u * R + lr, hi - 1)];
+    };
+    auto load = [&](int b, const int(&ix)[SLIDE_U], u32x4(&buf)[SLIDE_U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < SLIDE_U; ++u) {
+            const int d = min(b + u * R + lr, hi - 1);
+            GPTR(const char) src = d < e0 ? (GPTR(const char))plane + (size_t)ix[u] * a.row_bytes
+                                          : staged + (size_t)(d - e0) * staged_row;
+            buf[u] = NT ? __builtin_nontemporal_load((GPTR(const u32x4))src) : *(GPTR(const u32x4))src;
+        }
+    };
+    auto store = [&](int b, const u32x4(&buf)[SLIDE_U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < SLIDE_U; ++u) {
+            const int d = b + u * R + lr;
+            if (!mine || d >= hi) continue;
+            GPTR(u32x4) dst = (GPTR(u32x4))(plane + (size_t)d * a.row_bytes);
+            if (NT)
+                __builtin_nontemporal_store(buf[u], dst);
+            else
+                *dst = buf[u];
+        }
+    };
+    // a batch's source indices are loaded two batches ahead, before the rows of
+    // the batch in between: loads return in order, so that waiting for the
+    // indices never waits for those rows
+    int ia[SLIDE_U], ib[SLIDE_U];
+    u32x4 A[SLIDE_U], B[SLIDE_U];
+    load_idx(lo, ia);
+    load_idx(lo + N, ib);
+    load(lo, ia, A);
+    for (int b = lo; b < hi; b += 2 * N) {
+        load_idx(b + 2 * N, ia);
+        if (b + N < hi) load(b + N, ib, B);
+        store(b, A);
+        if (b + N >= hi) break;
+        load_idx(b + 3 * N, ib);
+        if (b + 2 * N < hi) load(b + 2 * N, ia, A);
+        store(b + N, B);
+    }
 }
+
+// Segments per strip: doubled while the waves are too few to fill the GPU and
+// the segments' tails fit the staging area; past SLIDE_FEW waves only while the
+// tails stay below 1/32 of the rows.  (512 strips: with 1024-row tails two segments
+// took 429 instead of 411 us, with 125-row tails 387 instead of 420; 32 strips of
+// a 2-layer cache: in 32 segments 82 us.)
+constexpr int SLIDE_FEW = 512, SLIDE_ENOUGH = 1024;
+static int slide_segments(int strips, int M, int n_evict, long long row_all, long long area) {
+    int s = 1;
+    while (strips * s < SLIDE_ENOUGH) {
+        const int t = 2 * s;
+        const long long tails = (long long)(t - 1) * std::min(n_evict, (M + t - 1) / t);
+        if (t > M || tails * row_all > area || (strips * s >= SLIDE_FEW && tails > M / 32)) break;
+        s = t;
+    }
+    return s;
+}
+// Moves of more bytes than the 256 MiB memory-side cache go past the caches
+// (nontemporal): 8192 rows of 64 KiB 249 -> 227 us, 16384 406 -> 382; smaller ones
+// through them: 8192 rows of 32 KiB 98 -> 80 us, of 16 KiB 89 -> 73.
+constexpr long long SLIDE_CACHED = 256ll << 20;
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -909,8 +821,6 @@ hipError_t kv_noalloc_scratch(char **out) {
 
 KvWorkspace kv_workspace_layout(int n_layers, int row_bytes, int capacity) {
     KvWorkspace w{};
-    const int ppg = GATHER_U / gather_kpr(row_bytes);
-    w.n_chunks = (2 * n_layers + ppg - 1) / ppg;
     const size_t cap = (size_t)capacity;
     const size_t blocks = (cap + SEL_BLOCK - 1) / SEL_BLOCK;
     size_t off = 0;
@@ -919,8 +829,6 @@ KvWorkspace kv_workspace_layout(int n_layers, int row_bytes, int capacity) {
     w.offPlanes = off;
     off = align256(off + KV_MAX_PLANES * sizeof(char *));
     w.offKeep = off;
-    off = align256(off + cap * 4);
-    w.offInv = off;
     off = align256(off + cap * 4);
     w.offThRun = off;
     off = align256(off + blocks * SEL_THREADS * 4);
@@ -934,18 +842,9 @@ KvWorkspace kv_workspace_layout(int n_layers, int row_bytes, int capacity) {
     off = align256(off + cap * 4);
     w.offRunFrom = off;
     off = align256(off + cap * 4);
-    w.offFlags = off;
-    off = align256(off + cap * (size_t)w.n_chunks * 4);
-    w.stage_rows = 0;
-    w.offStage = w.offStageMeta = off;
-    if (w.n_chunks > 0) {
-        const long long per_row = (long long)w.n_chunks * GATHER_U * 16 * 256;
-        w.stage_rows = (int)std::max(1ll, std::min((long long)capacity, STAGE_AREA / per_row));
-        w.offStage = off;
-        off = align256(off + (size_t)w.stage_rows * per_row);
-        w.offStageMeta = off;
-        off = align256(off + (size_t)w.stage_rows * 8);
-    }
+    w.offStage = off;  // tails of the segments of kv_slide
+    w.stage_bytes = (size_t)std::min(STAGE_AREA, (long long)capacity * 2 * n_layers * row_bytes);
+    off = align256(off + w.stage_bytes);
     w.total = off;
     return w;
 }
@@ -997,25 +896,14 @@ hipError_t launch_kv_evict(const KvLaunch &p, hipStream_t stream) {
     a.n_s = p.n_sink;
     a.n_w = p.n_window;
     a.N = p.n_buckets;
-    a.n_flags = p.M * p.lay.n_chunks;
-    a.n_chunks = p.lay.n_chunks;
-    {
-        // stage destinations whose shift spans less than STAGE_BYTES of rows
-        const long long row_all = (long long)std::max(p.n_planes, 1) * p.row_bytes;
-        a.stage_shift = (int)std::min((long long)p.M + 1, (STAGE_BYTES + row_all - 1) / row_all);
-        if (p.slot) a.stage_shift = p.M + 1;  // the indexed variant moves no rows
-    }
     a.status = (int32_t *)(ws + p.lay.offStatus);
-    a.ticket = (uint32_t *)(ws + p.lay.offStatus + 32);
     a.keep = (int32_t *)(ws + p.lay.offKeep);
-    a.inv = (int32_t *)(ws + p.lay.offInv);
     a.th_run = (int32_t *)(ws + p.lay.offThRun);
     a.run_start = (int32_t *)(ws + p.lay.offRunStart);
     a.run_key = (unsigned long long *)(ws + p.lay.offRunKey);
     a.run_bkt = (int32_t *)(ws + p.lay.offRunBkt);
     a.run_take = (int32_t *)(ws + p.lay.offRunTake);
     a.run_from = (int32_t *)(ws + p.lay.offRunFrom);
-    a.flags = (int32_t *)(ws + p.lay.offFlags);
     a.keep_out = p.keep_out;
     a.slot = p.slot;
     a.free_out = p.free_out;
@@ -1027,75 +915,45 @@ hipError_t launch_kv_evict(const KvLaunch &p, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.slot) return e;  // the indexed variant moves no rows
 
-    const long long groups = (long long)p.M * p.lay.n_chunks;
-    if (groups == 0) return hipSuccess;
-    GatherArgs g;
-    const int kpr = gather_kpr(p.row_bytes);
+    if (p.M == 0) return hipSuccess;
+    SlideArgs g;
     g.plane_tab = a.plane_tab;
     g.row_bytes = (uint32_t)p.row_bytes;
     g.row_units = (uint32_t)(p.row_bytes / 16);
     g.n_planes = p.n_planes;
-    g.planes_per_group = GATHER_U / kpr;
-    g.trash = ws + p.lay.offStage;
     g.M = p.M;
-    g.n_chunks = p.lay.n_chunks;
+    g.n_evict = p.len - p.M;
     g.pos = p.pos;
     g.chunk = p.chunk_id;
     g.keep = a.keep;
-    g.inv = a.inv;
-    g.flags = a.flags;
     g.status = a.status;
-    g.ticket = a.ticket;
-    // staged destinations first (block by block, in order), then the ticket gather
-    StageArgs sa;
-    sa.plane_tab = a.plane_tab;
-    sa.row_bytes = g.row_bytes;
-    sa.row_units = g.row_units;
-    sa.n_planes = p.n_planes;
-    sa.planes_per_group = g.planes_per_group;
-    sa.n_chunks = p.lay.n_chunks;
-    sa.rows = p.lay.stage_rows;
-    sa.pos = p.pos;
-    sa.chunk = p.chunk_id;
-    sa.keep = a.keep;
-    sa.status = a.status;
-    sa.area = p.ws + p.lay.offStage;
-    sa.meta = (int32_t *)(p.ws + p.lay.offStageMeta);
-    const dim3 sgrid((unsigned)std::min(sa.rows, STAGE_WG), (unsigned)sa.n_chunks), blk(256);
-    for (int b = 0; (long long)b * sa.rows < p.M; ++b) {
-        sa.block = b;
-        switch (kpr) {
-        case 1:
-            hipLaunchKernelGGL((kv_stage_kernel<1, true>), sgrid, blk, 0, stream, sa);
-            hipLaunchKernelGGL((kv_stage_kernel<1, false>), sgrid, blk, 0, stream, sa);
-            break;
-        case 2:
-            hipLaunchKernelGGL((kv_stage_kernel<2, true>), sgrid, blk, 0, stream, sa);
-            hipLaunchKernelGGL((kv_stage_kernel<2, false>), sgrid, blk, 0, stream, sa);
-            break;
-        case 4:
-            hipLaunchKernelGGL((kv_stage_kernel<4, true>), sgrid, blk, 0, stream, sa);
-            hipLaunchKernelGGL((kv_stage_kernel<4, false>), sgrid, blk, 0, stream, sa);
-            break;
-        case 8:
-            hipLaunchKernelGGL((kv_stage_kernel<8, true>), sgrid, blk, 0, stream, sa);
-            hipLaunchKernelGGL((kv_stage_kernel<8, false>), sgrid, blk, 0, stream, sa);
-            break;
-        default:
-            hipLaunchKernelGGL((kv_stage_kernel<16, true>), sgrid, blk, 0, stream, sa);
-            hipLaunchKernelGGL((kv_stage_kernel<16, false>), sgrid, blk, 0, stream, sa);
-            break;
-        }
+    g.area = ws + p.lay.offStage;
+    // lanes per strip: 128 bytes, or the whole row where it is shorter
+    int lpr = 1;
+    while (lpr < 8 && lpr < (int)g.row_units) lpr *= 2;
+    g.strips = ((int)g.row_units + lpr - 1) / lpr;
+    g.segments = slide_segments(p.n_planes * g.strips, p.M, g.n_evict, (long long)p.n_planes * p.row_bytes,
+                                (long long)p.lay.stage_bytes);
+    g.seg_tail = std::min(g.n_evict, (p.M + g.segments - 1) / g.segments);
+    if (g.segments > 1) {
+        hipLaunchKernelGGL(kv_stage_tails_kernel, dim3(g.seg_tail, g.segments - 1), dim3(256), 0, stream, g);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const dim3 grid((unsigned)std::min((p.M + GATHER_ROWS - 1) / GATHER_ROWS, GATHER_WG));
-    switch (kpr) {
-    case 1: hipLaunchKernelGGL(kv_gather_kernel<1>, grid, blk, 0, stream, g); break;
-    case 2: hipLaunchKernelGGL(kv_gather_kernel<2>, grid, blk, 0, stream, g); break;
-    case 4: hipLaunchKernelGGL(kv_gather_kernel<4>, grid, blk, 0, stream, g); break;
-    case 8: hipLaunchKernelGGL(kv_gather_kernel<8>, grid, blk, 0, stream, g); break;
-    default: hipLaunchKernelGGL(kv_gather_kernel<16>, grid, blk, 0, stream, g); break;
+    // the first workgroup moves positions and chunk ids
+    const dim3 grid(1 + (unsigned)((p.n_planes * g.strips * g.segments + SLIDE_WAVES - 1) / SLIDE_WAVES)), blk(64 * SLIDE_WAVES);
+    auto slide = [&](auto lc) {
+        constexpr int L = decltype(lc)::value;
+        if ((long long)p.M * p.n_planes * p.row_bytes > SLIDE_CACHED)
+            hipLaunchKernelGGL((kv_slide_kernel<L, true>), grid, blk, 0, stream, g);
+        else
+            hipLaunchKernelGGL((kv_slide_kernel<L, false>), grid, blk, 0, stream, g);
+    };
+    switch (lpr) {
+    case 1: slide(std::integral_constant<int, 1>()); break;
+    case 2: slide(std::integral_constant<int, 2>()); break;
+    case 4: slide(std::integral_constant<int, 4>()); break;
+    default: slide(std::integral_constant<int, 8>()); break;
     }
     return hipGetLastError();
 }

@@ -394,3 +394,25 @@ def test_append_indexed_matches_indexing(ds, na, nb, T, n, row):
         assert torch.equal(t, e)
     r = na + nb - T
     assert torch.equal(rest[:r], lst[T:].to(torch.int32)) and bool((rest[r:] == -9).all())
+
+
+@pytest.mark.parametrize("L,row_elems", [(1, 8), (1, 24), (3, 72), (2, 1032), (1, 2048), (16, 64)])
+@pytest.mark.parametrize("n,M,step", [(700, 699, 1), (1500, 900, 40), (2000, 64, 50), (4100, 4000, 100), (3001, 1500, 7)])
+def test_strips_and_segments(ds, L, row_elems, n, M, step):
+    """The in-place move at its edges: rows of one 16-byte unit, rows that end in
+    the middle of a 128-byte strip, few planes (many segments, whose tails are
+    staged) and many; one evicted token, tails longer than a segment, more
+    evicted than kept, a budget smaller than a batch of rows.  Scores with many
+    ties; the tokens evicted are spread over spans."""
+    rng = np.random.default_rng(n + M + L + row_elems)
+    chunk = (np.arange(n) // step).astype(np.int32)
+    pos = (np.arange(n) * 2 + 5).astype(np.int32)
+    scores = rng.choice([0.1, 0.2, 0.4, 0.8], size=int(chunk[-1]) + 1).astype(np.float32)
+    one_event(ds, L, row_elems, chunk, pos, scores, M, min(4, M // 8), M // 10, 3, capacity=n + 13)
+
+
+def test_many_strips_of_wide_rows(ds):
+    """64 KiB rows (512 strips a plane) and a first chunk evicted: every row moves, in one segment."""
+    chunk = np.repeat(np.arange(5), 60).astype(np.int32)
+    scores = np.array([0.1, 1, 1, 1, 1], np.float32)
+    one_event(ds, 1, 32768, chunk, np.arange(300, dtype=np.int32), scores, 240, 0, 0, 1)
