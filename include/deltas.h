@@ -164,6 +164,27 @@ ds_status gdn_chunk_fwd(const ds_gdn_shape *shape, const void *q, const void *k,
                         void *workspace, size_t workspace_bytes, void *stream);
 
 /* ------------------------------------------------------------------------
+ * gdn_layers_fwd -- gdn_chunk_fwd over independent layers of equal length
+ * ------------------------------------------------------------------------
+ * The same computation for shape->B layers (or streams) of T = T_total / B
+ * tokens each, in one call, where layer b's rows start at token b * pitch of
+ * every token array (pitch >= T; the rows between are neither read nor
+ * written): q, k, v, g, beta and o are [B][pitch][heads](...), the states
+ * [B][H_v][d_v][d_k], the drift pairs numbered layer by layer as the frames of
+ * streams are.  The workspace is that of ds_gdn_workspace_bytes(shape).
+ */
+ds_status gdn_layers_fwd(const ds_gdn_shape *shape, int32_t pitch, const void *q, const void *k, const void *v,
+                         const float *g, const float *beta, const float *state_in, float *state_out, void *o,
+                         int32_t o_dtype, float scale, float *drift_partials, void *workspace,
+                         size_t workspace_bytes, void *stream);
+
+/* Separate per-layer inputs of T tokens to the layout of gdn_layers_fwd:
+ * src[i * n_layers + l] is array i (0 - 4: q, k, v, g, beta) of layer l, dst[i]
+ * array i of every layer, layer l from token l * pitch on. */
+ds_status gdn_pack_layers(int32_t n_layers, int32_t T, int32_t pitch, int32_t H_k, int32_t H_v, int32_t d,
+                          const void *const *src, void *const *dst, void *stream);
+
+/* ------------------------------------------------------------------------
  * gdn_decode_step -- one token of Eq. 2 for each of B streams
  * ------------------------------------------------------------------------
  * For every stream b and v-head j (reading qk-head j * H_k / H_v), with

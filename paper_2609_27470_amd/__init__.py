@@ -24,7 +24,7 @@ EXPORTED = [
     "gdn_chunk_fwd", "deltas_drift",
     "deltas_drift_states", "ds_kv_workspace_bytes", "kv_evict_topk", "ds_kv_device_status",
     "ds_kv_indexed_workspace_bytes", "kv_evict_topk_indexed", "gdn_decode_step", "kv_evict_topk_indexed_noalloc",
-    "kv_append_indexed",
+    "kv_append_indexed", "gdn_layers_fwd", "gdn_pack_layers",
 ]
 NOALLOC_MAX_CAPACITY = 65536
 
@@ -89,6 +89,11 @@ def lib():
         L.kv_evict_topk_indexed_noalloc.restype = I32
         L.kv_append_indexed.argtypes = [P, P, I32, I32, I32, P, I32, P, I32, P, I32, I32, I32, I32, P, P, P, P]
         L.kv_append_indexed.restype = I32
+        L.gdn_layers_fwd.argtypes = [ctypes.POINTER(GdnShape), I32, P, P, P, P, P, P, P, P, I32, ctypes.c_float, P, P,
+                                     SZ, P]
+        L.gdn_layers_fwd.restype = I32
+        L.gdn_pack_layers.argtypes = [I32, I32, I32, I32, I32, I32, P, P, P]
+        L.gdn_pack_layers.restype = I32
         _lib = L
     return _lib
 
@@ -171,6 +176,47 @@ def gdn_chunk_fwd(q, k, v, g, beta, lengths, frame_len, cu_seqlens=None, state_i
                                _ptr(cu_seqlens), _ptr(state_in), _ptr(state_out), _ptr(o), od, float(scale),
                                _ptr(dp), _ptr(wp), _ptr(sn), _ptr(workspace), workspace.numel(), _stream(stream)))
     return dict(o=o, state=state_out, drift_partials=dp, write_partials=wp, snapshots=sn, workspace=workspace)
+
+
+def gdn_layers_fwd(q, k, v, g, beta, T, state, o, drift_partials, workspace, scale=1.0, stream=None,
+                   drift_per_slice=False):
+    """The first T tokens of every layer as one frame each, in one call, the states updated in place (see
+    gdn_layers_fwd in deltas.h).
+
+    q, k: bf16 [L][pitch][H_k][d]; v: bf16 [L][pitch][H_v][d]; g, beta: fp32 [L][pitch][H_v]; o: bf16 or fp32
+    [L][pitch][H_v][d]; state: fp32 [L][...H_v][d][d]; drift_partials: fp32 [L][...pairs][2]; workspace of
+    gdn_workspace_bytes(gdn_shape([T] * L, ...)).
+    """
+    L, pitch, H_k, d = q.shape
+    H_v = v.shape[2]
+    if k.shape != q.shape or v.shape != (L, pitch, H_v, d) or o.shape != v.shape or g.shape != (L, pitch, H_v) \
+            or beta.shape != g.shape:
+        raise ValueError("shape mismatch")
+    pairs = H_v * (d // 16) if drift_per_slice else H_v
+    if state.numel() != L * H_v * d * d or drift_partials.numel() != L * pairs * 2:
+        raise ValueError("state or drift_partials of another size")
+    for t in (q, k, v, g, beta, state, o, drift_partials):
+        if not t.is_contiguous():
+            raise ValueError("every array must be contiguous")
+    shape = GdnShape(L, L * int(T), H_k, H_v, d, d, 0, L, int(bool(drift_per_slice)))
+    od = DS_BF16 if o.dtype == torch.bfloat16 else DS_F32
+    _check(lib().gdn_layers_fwd(ctypes.byref(shape), pitch, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
+                                _ptr(state), _ptr(state), _ptr(o), od, float(scale), _ptr(drift_partials),
+                                _ptr(workspace), workspace.numel(), _stream(stream)))
+
+
+def gdn_pack_layers(layer_inputs, T, packed, stream=None):
+    """The first T rows of every layer's (q, k, v, g, beta) into the packed arrays [L][pitch]... of gdn_layers_fwd."""
+    L, pitch, H_k, d = packed[0].shape
+    H_v = packed[2].shape[2]
+    rows = [p.shape[2:] for p in packed]
+    for x in layer_inputs:
+        for t, p, r in zip(x, packed, rows):
+            if t.element_size() != p.element_size() or t.shape[0] < T or t.shape[1:] != r:
+                raise ValueError("a layer's inputs are not (q, k, v, g, beta) of the session's heads")
+    src = (ctypes.c_void_p * (5 * L))(*[x[i].data_ptr() for i in range(5) for x in layer_inputs])
+    dst = (ctypes.c_void_p * 5)(*[p.data_ptr() for p in packed])
+    _check(lib().gdn_pack_layers(L, int(T), pitch, H_k, H_v, d, src, dst, _stream(stream)))
 
 
 def deltas_drift(partials, mode=LAYER_FROB, scores=None, stream=None):
@@ -326,6 +372,12 @@ def kv_outcome_word(workspace):
     return workspace[:4].view(torch.int32)
 
 
+def _layer_ptrs(t):
+    """The addresses of t[0], t[1], ... (no tensor is made for each)."""
+    base, step = t.data_ptr(), t.stride(0) * t.element_size()
+    return range(base, base + step * t.shape[0], step) if step > 0 else [base] * t.shape[0]
+
+
 def kv_append_indexed(k_planes, v_planes, k_new, v_new, free_a, na, free_b, nb, free_rest, T, n, pos0, chunk, pos,
                       chunk_id, slot, stream=None):
     """A chunk's rows into a slot-indexed cache (see kv_append_indexed in
@@ -346,10 +398,8 @@ def kv_append_indexed(k_planes, v_planes, k_new, v_new, free_a, na, free_b, nb, 
         if t.dtype != torch.int32 or t.numel() != capacity:
             raise ValueError("pos, chunk_id and slot must be int32 tensors of the cache capacity")
     row_bytes = row * k_planes.element_size()
-    planes = (ctypes.c_void_p * (2 * L))(*[k_planes[l].data_ptr() for l in range(L)],
-                                         *[v_planes[l].data_ptr() for l in range(L)])
-    rows = (ctypes.c_void_p * (2 * L))(*[k_new[l].data_ptr() for l in range(L)],
-                                       *[v_new[l].data_ptr() for l in range(L)])
+    planes = (ctypes.c_void_p * (2 * L))(*_layer_ptrs(k_planes), *_layer_ptrs(v_planes))
+    rows = (ctypes.c_void_p * (2 * L))(*_layer_ptrs(k_new), *_layer_ptrs(v_new))
     _check(lib().kv_append_indexed(planes, rows, 2 * L, row_bytes, capacity, _ptr(free_a), int(na), _ptr(free_b),
                                    int(nb), _ptr(free_rest), int(T), int(n), int(pos0), int(chunk), _ptr(pos),
                                    _ptr(chunk_id), _ptr(slot), _stream(stream)))

@@ -78,19 +78,19 @@ size_t ds_gdn_write_workspace_bytes(const ds_gdn_shape *shape) {
         .total;
 }
 
-ds_status gdn_chunk_fwd(const ds_gdn_shape *shape, const void *q, const void *k, const void *v, const float *g,
-                        const float *beta, const int32_t *cu_seqlens, const float *state_in, float *state_out,
-                        void *o, int32_t o_dtype, float scale, float *drift_partials, float *write_partials,
-                        float *snapshots,
-                        void *workspace, size_t workspace_bytes, void *stream) {
-    g_last_error[0] = 0;
+// gdn_chunk_fwd (pitch 0) and gdn_layers_fwd
+static ds_status gdn_forward(const ds_gdn_shape *shape, int32_t pitch, const void *q, const void *k, const void *v,
+                             const float *g, const float *beta, const int32_t *cu_seqlens, const float *state_in,
+                             float *state_out, void *o, int32_t o_dtype, float scale, float *drift_partials,
+                             float *write_partials, float *snapshots, void *workspace, size_t workspace_bytes,
+                             void *stream) {
     ds_status st = check_gdn_shape(shape);
     if (st != DS_OK) return st;
     const ds_gdn_shape &s = *shape;
     if (s.T_total > 0 && (!q || !k || !v || !g || !beta || !o))
         return fail(DS_E_NULL, "q, k, v, g, beta and o are required");
     if (!state_out) return fail(DS_E_NULL, "state_out is required");
-    if (s.B > 1 && !cu_seqlens) return fail(DS_E_NULL, "cu_seqlens is required when B > 1");
+    if (s.B > 1 && !cu_seqlens && !pitch) return fail(DS_E_NULL, "cu_seqlens is required when B > 1");
     if (o_dtype != DS_BF16 && o_dtype != DS_F32) return fail(DS_E_DTYPE, "o_dtype=%d", o_dtype);
     const void *ptrs[] = {q, k, v, g, beta, cu_seqlens, state_in, state_out, o, drift_partials, write_partials,
                           snapshots, workspace};
@@ -114,6 +114,7 @@ ds_status gdn_chunk_fwd(const ds_gdn_shape *shape, const void *q, const void *k,
     p.cu_seqlens = cu_seqlens;
     p.B = s.B;
     p.T_total = s.T_total;
+    p.pitch = pitch;
     p.H_k = s.H_k;
     p.H_v = s.H_v;
     p.d = s.d_k;
@@ -140,7 +141,65 @@ ds_status gdn_chunk_fwd(const ds_gdn_shape *shape, const void *q, const void *k,
     p.tiles_max = lay.tiles_max;
     p.n_split = lay.n_split;
     hipError_t e = ds::launch_gdn(p, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "gdn_chunk_fwd launch");
+    if (e != hipSuccess) return hip_fail(e, pitch ? "gdn_layers_fwd launch" : "gdn_chunk_fwd launch");
+    return DS_OK;
+}
+
+ds_status gdn_chunk_fwd(const ds_gdn_shape *shape, const void *q, const void *k, const void *v, const float *g,
+                        const float *beta, const int32_t *cu_seqlens, const float *state_in, float *state_out,
+                        void *o, int32_t o_dtype, float scale, float *drift_partials, float *write_partials,
+                        float *snapshots,
+                        void *workspace, size_t workspace_bytes, void *stream) {
+    g_last_error[0] = 0;
+    return gdn_forward(shape, 0, q, k, v, g, beta, cu_seqlens, state_in, state_out, o, o_dtype, scale, drift_partials,
+                       write_partials, snapshots, workspace, workspace_bytes, stream);
+}
+
+ds_status gdn_layers_fwd(const ds_gdn_shape *shape, int32_t pitch, const void *q, const void *k, const void *v,
+                         const float *g, const float *beta, const float *state_in, float *state_out, void *o,
+                         int32_t o_dtype, float scale, float *drift_partials, void *workspace,
+                         size_t workspace_bytes, void *stream) {
+    g_last_error[0] = 0;
+    if (!shape) return fail(DS_E_NULL, "shape is NULL");
+    if (shape->B < 1 || shape->T_total < shape->B || shape->T_total % shape->B != 0)
+        return fail(DS_E_SHAPE, "T_total=%d is not a positive multiple of B=%d", shape->T_total, shape->B);
+    if (pitch < shape->T_total / shape->B)
+        return fail(DS_E_SHAPE, "pitch=%d is less than the %d tokens of a layer", pitch, shape->T_total / shape->B);
+    if (shape->H_v >= 1 && (long long)pitch * shape->B > (1LL << 30) / shape->H_v)
+        return fail(DS_E_UNSUPPORTED, "problem too large for one call");
+    return gdn_forward(shape, pitch, q, k, v, g, beta, nullptr, state_in, state_out, o, o_dtype, scale, drift_partials,
+                       nullptr, nullptr, workspace, workspace_bytes, stream);
+}
+
+ds_status gdn_pack_layers(int32_t n_layers, int32_t T, int32_t pitch, int32_t H_k, int32_t H_v, int32_t d,
+                          const void *const *src, void *const *dst, void *stream) {
+    g_last_error[0] = 0;
+    if (n_layers < 1 || T < 1 || pitch < T || H_k < 1 || H_v < 1 || d < 8 || d % 8 != 0)
+        return fail(DS_E_SHAPE, "n_layers=%d T=%d pitch=%d H_k=%d H_v=%d d=%d", n_layers, T, pitch, H_k, H_v, d);
+    if (!src || !dst) return fail(DS_E_NULL, "src and dst are required");
+    const long long row[5] = {(long long)H_k * d / 8, (long long)H_k * d / 8, (long long)H_v * d / 8, H_v, H_v};
+    for (int i = 0; i < 5; ++i) {
+        if (row[i] * T > (1LL << 31) - 1) return fail(DS_E_UNSUPPORTED, "problem too large for one call");
+        if (!dst[i]) return fail(DS_E_NULL, "dst[%d] is NULL", i);
+        if (misaligned(dst[i])) return fail(DS_E_ALIGN, "a pointer is not 16-byte aligned");
+        for (int l = 0; l < n_layers; ++l) {
+            const void *p = src[(size_t)i * n_layers + l];
+            if (!p) return fail(DS_E_NULL, "src of array %d, layer %d is NULL", i, l);
+            if (misaligned(p)) return fail(DS_E_ALIGN, "a pointer is not 16-byte aligned");
+        }
+    }
+    for (int l0 = 0; l0 < n_layers; l0 += ds::PACK_LAYERS) {
+        const int n = n_layers - l0 < ds::PACK_LAYERS ? n_layers - l0 : ds::PACK_LAYERS;
+        ds::GdnPack p{};
+        for (int i = 0; i < 5; ++i) {
+            p.words[i] = (uint32_t)(row[i] * T);
+            p.layer_words[i] = (size_t)row[i] * pitch;
+            p.dst[i] = (char *)dst[i] + (size_t)l0 * p.layer_words[i] * (i < 3 ? 16 : 4);
+            for (int l = 0; l < n; ++l) p.src[i][l] = src[(size_t)i * n_layers + l0 + l];
+        }
+        const hipError_t e = ds::launch_gdn_pack(p, n, (hipStream_t)stream);
+        if (e != hipSuccess) return hip_fail(e, "gdn_pack_layers launch");
+    }
     return DS_OK;
 }
 

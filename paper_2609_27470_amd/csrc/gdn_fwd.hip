@@ -1152,7 +1152,7 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     a.v = p.v;
     a.g = p.g;
     a.beta = p.beta;
-    a.st = Streams{p.cu_seqlens, p.B, p.T_total};
+    a.st = p.pitch ? pitched_streams(p.B, p.T_total / p.B, p.pitch) : Streams{p.cu_seqlens, p.B, p.T_total};
     a.H_k = p.H_k;
     a.H_v = p.H_v;
     a.group = p.H_v / p.H_k;
@@ -1259,6 +1259,36 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
         e = hipGetLastError();
     }
     return e;
+}
+
+// Workgroup (x, layer, array): the layer's rows of one array into the packed
+// buffer, four words per thread.
+template <typename W>
+__device__ __forceinline__ void pack_words(const W *src, W *dst, uint32_t n) {
+    const uint32_t i0 = blockIdx.x * 1024u + threadIdx.x;
+    W x[4];
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c)
+        if (i0 + 256 * c < n) x[c] = src[i0 + 256 * c];
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c)
+        if (i0 + 256 * c < n) dst[i0 + 256 * c] = x[c];
+}
+__global__ __launch_bounds__(256) void gdn_pack_kernel(GdnPack p) {
+    const int l = blockIdx.y, i = blockIdx.z;
+    if (blockIdx.x * 1024u >= p.words[i]) return;
+    if (i < 3)
+        pack_words((const u32x4 *)p.src[i][l], (u32x4 *)p.dst[i] + l * p.layer_words[i], p.words[i]);
+    else
+        pack_words((const uint32_t *)p.src[i][l], (uint32_t *)p.dst[i] + l * p.layer_words[i], p.words[i]);
+}
+
+hipError_t launch_gdn_pack(const GdnPack &p, int n_layers, hipStream_t stream) {
+    uint32_t most = 0;
+    for (uint32_t w : p.words) most = w > most ? w : most;
+    if (most == 0 || n_layers == 0) return hipSuccess;
+    hipLaunchKernelGGL(gdn_pack_kernel, dim3((most + 1023) / 1024, n_layers, 5), dim3(256), 0, stream, p);
+    return hipGetLastError();
 }
 
 hipError_t launch_gdn(const GdnLaunch &p, hipStream_t stream) {

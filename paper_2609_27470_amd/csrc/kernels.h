@@ -12,6 +12,7 @@ struct GdnLaunch {
     const float *g, *beta;
     const int32_t *cu_seqlens;
     int B, T_total, H_k, H_v, d;  // d = d_k = d_v
+    int pitch;                    // 0: packed streams; else stream b's T_total / B tokens start at token b * pitch
     int frame_len, n_frames;
     const float *state_in;
     float *state_out;
@@ -43,6 +44,16 @@ struct GdnWorkspace {
 // with_write: also the per-token norm area of the write signal (write_partials != NULL)
 GdnWorkspace gdn_workspace_layout(int B, int T_total, int H_k, int H_v, int d, int n_frames, bool with_write);
 hipError_t launch_gdn(const GdnLaunch &p, hipStream_t stream);
+
+// The inputs of up to PACK_LAYERS layers (one launch), five arrays each, to one buffer per array.
+constexpr int PACK_LAYERS = 64;
+struct GdnPack {
+    const void *src[5][PACK_LAYERS];
+    void *dst[5];         // first layer's rows
+    uint32_t words[5];    // 16-byte (q, k, v) or 4-byte (g, beta) words to copy per layer
+    size_t layer_words[5];  // words from one layer's rows to the next in dst
+};
+hipError_t launch_gdn_pack(const GdnPack &p, int n_layers, hipStream_t stream);
 
 // ---------------------------------------------------------------- decode step
 struct DecodeArgs {

@@ -18,16 +18,14 @@ Only argument marshalling and buffer bookkeeping happen here; every step of
 the computation runs in the HIP kernels behind the C ABI.  The snapshot
 copies are plain device copies.
 
-A chunk is a tiny call per layer (about 125 tokens), so launching the layers
-one by one from the host costs more than the kernels themselves.
-`capture_graph` records all layers and the score of one chunk in a HIP graph
-over fixed input buffers (`inputs`); the chunk's length is read on the
-device, so a graph serves every chunk length up to the capacity it was
-recorded for.  Two are recorded: one for chunks of at most two tiles
-(SMALL_CHUNK tokens), whose layer calls take the library's one-launch path,
-and one for max_chunk.  The
-append and the eviction stay outside the graph: the cache length they work
-from is host state.
+A chunk is a tiny call per layer (about 125 tokens) that leaves most of the GPU
+idle, and the inputs of all layers are there before the first one runs: the
+layers go through `gdn_layers_fwd` together (24 layers x 125 tokens x 32 heads,
+append and eviction included: 142 us a chunk; with a launch per layer, replayed
+as a HIP graph, 434 us).
+`capture_graph` allocates input buffers in that call's layout (`inputs`);
+`step_inputs` runs a chunk that the caller has written there, `step` first
+brings separate per-layer tensors into such a layout of its own.
 
 By default (`indexed=True`) the cache is addressed through a slot table
 (logical token i lives in physical row slot[i]): eviction is
@@ -49,11 +47,13 @@ from dataclasses import dataclass
 
 import torch
 
-from . import (LAYER_FROB, deltas_drift, gdn_chunk_fwd, gdn_shape, gdn_workspace_bytes, kv_append_indexed,
-               kv_evict_topk, kv_evict_topk_indexed, kv_indexed_workspace_bytes, kv_outcome_word, kv_workspace_bytes)
+from . import (LAYER_FROB, deltas_drift, gdn_layers_fwd, gdn_pack_layers, gdn_shape, gdn_workspace_bytes,
+               kv_append_indexed, kv_evict_topk, kv_evict_topk_indexed, kv_indexed_workspace_bytes, kv_outcome_word,
+               kv_workspace_bytes)
 
-# the longest chunk whose layer calls fit two 64-token tiles
-SMALL_CHUNK = 128
+# at most this much workspace for the layers that one call takes together (76 MiB for 24 layers of 32 heads and 132
+# tokens; sessions of much longer chunks run their layers in groups, each of which fills the GPU by itself)
+LAYERS_WORKSPACE = 1 << 30
 
 
 class EvictionFailed(RuntimeError):
@@ -115,8 +115,13 @@ class DeltaSStream:
         self.pos = torch.zeros(self.capacity, dtype=torch.int32, device=dev)
         self.chunk_id = torch.zeros(self.capacity, dtype=torch.int32, device=dev)
         self.scores = torch.zeros(max_chunks, dtype=torch.float32, device=dev)
-        shape = gdn_shape([max_chunk], H_k, H_v, d, 0)
-        self.gdn_ws = torch.empty(max(gdn_workspace_bytes(shape), 1), dtype=torch.uint8, device=dev)
+        need = lambda n: gdn_workspace_bytes(gdn_shape([max_chunk] * n, H_k, H_v, d, 0))  # noqa: E731
+        self.group = n_layers   # layers per call
+        while self.group > 1 and not 0 < need(self.group) <= LAYERS_WORKSPACE:   # (0: too large for one call)
+            self.group = (self.group + 1) // 2
+        rest = n_layers % self.group
+        self.gdn_ws = torch.empty(max(need(self.group), need(rest) if rest else 0, 1), dtype=torch.uint8, device=dev)
+        self.inputs = self._packed = None
         self.indexed = indexed
         if indexed:
             self.slot = torch.zeros(self.capacity, dtype=torch.int32, device=dev)
@@ -133,7 +138,6 @@ class DeltaSStream:
             self.kv_ws = torch.empty(max(kv_workspace_bytes(kv_layers, row_elems * 2, self.capacity), 1),
                                      dtype=torch.uint8, device=dev)
         self.kv_fail = torch.zeros(1, dtype=torch.int32, device=dev)   # max outcome word of every eviction
-        self.graph = None
         self.length = 0      # tokens in the cache
         self.n_chunks = 0    # chunks seen (the next chunk's id)
         self.next_pos = 0    # position of the next token
@@ -170,16 +174,14 @@ class DeltaSStream:
             raise ValueError(f"chunk of {T} tokens (1..{self.max_chunk})")
         if len(layer_inputs) != self.L:
             raise ValueError("one input tuple per linear-attention layer")
-        c = self.n_chunks
-        if c >= self.scores.numel():
+        if self.n_chunks >= self.scores.numel():
             raise ValueError("score table full")
         # every launch and copy of the step on one stream (the caller's, else the current one)
         with _on(stream):
-            for l, (q, k, v, g, beta) in enumerate(layer_inputs):
-                st = self.state[l]
-                gdn_chunk_fwd(q, k, v, g, beta, [T], 0, state_in=st, state_out=st, o=self.o[l, :T],
-                              drift_partials=self.partials[l], workspace=self.gdn_ws, drift_per_slice=self.per_slice)
-            deltas_drift(self.partials, self.score_mode, scores=self.scores[c:c + 1])
+            if self._packed is None:
+                self._packed = self._input_buffers(torch.empty)
+            gdn_pack_layers(layer_inputs, T, self._packed)
+            self._layers(T, self._packed)
             return self._append_and_evict(T, k_rows, v_rows)
 
     def check(self):
@@ -229,50 +231,37 @@ class DeltaSStream:
         idx = self.slot[:n].to(torch.int64)
         return self.k[:, idx], self.v[:, idx]
 
-    def capture_graph(self):
-        """Allocate the fixed input buffers and record one chunk's linear-attention
-        work (every layer, then the chunk score) as a HIP graph; see step_inputs."""
-        L, Tm, H_k, H_v, d, dev = self.L, self.max_chunk, self.H_k, self.H_v, self.d, self.dev
-        self.inputs = (torch.zeros((L, Tm, H_k, d), dtype=torch.bfloat16, device=dev),
-                       torch.zeros((L, Tm, H_k, d), dtype=torch.bfloat16, device=dev),
-                       torch.zeros((L, Tm, H_v, d), dtype=torch.bfloat16, device=dev),
-                       torch.zeros((L, Tm, H_v), dtype=torch.float32, device=dev),
-                       torch.zeros((L, Tm, H_v), dtype=torch.float32, device=dev))
-        self.cu = torch.tensor([0, Tm], dtype=torch.int32, device=dev)
-        self.score_buf = torch.zeros(1, dtype=torch.float32, device=dev)
-        self.graphs = {}
-        for cap in sorted({min(Tm, SMALL_CHUNK), Tm}):
-            torch.cuda.synchronize()
-            g = torch.cuda.CUDAGraph()
-            with torch.cuda.graph(g):
-                self._layers_fixed(cap)
-            torch.cuda.synchronize()
-            self.graphs[cap] = g
-        self.graph = self.graphs[Tm]
+    def _input_buffers(self, make):
+        L, Tm, dev = self.L, self.max_chunk, self.dev
+        new = lambda dt, *s: make((L, Tm) + s, dtype=dt, device=dev)  # noqa: E731
+        return (new(torch.bfloat16, self.H_k, self.d), new(torch.bfloat16, self.H_k, self.d),
+                new(torch.bfloat16, self.H_v, self.d), new(torch.float32, self.H_v), new(torch.float32, self.H_v))
 
-    def _layers_fixed(self, cap):
-        q, k, v, g, b = self.inputs
-        for l in range(self.L):
-            st = self.state[l]
-            gdn_chunk_fwd(q[l], k[l], v[l], g[l], b[l], [cap], 0, cu_seqlens=self.cu, state_in=st,
-                          state_out=st, o=self.o[l], drift_partials=self.partials[l], workspace=self.gdn_ws,
-                          drift_per_slice=self.per_slice)
-        deltas_drift(self.partials, self.score_mode, scores=self.score_buf)
+    def capture_graph(self):
+        """Allocate the input buffers (q, k, v, g, beta, each [layer][max_chunk]...) of step_inputs."""
+        self.inputs = self._input_buffers(torch.zeros)
+
+    def _layers(self, T, x):
+        """Every layer over the first T tokens of x, then the chunk's score."""
+        c = self.n_chunks
+        for a in range(0, self.L, self.group):
+            q, k, v, g, beta = x if self.group == self.L else (t[a:a + self.group] for t in x)
+            b = a + self.group
+            gdn_layers_fwd(q, k, v, g, beta, T, self.state[a:b], self.o[a:b], self.partials[a:b], self.gdn_ws,
+                           drift_per_slice=self.per_slice)
+        deltas_drift(self.partials, self.score_mode, scores=self.scores[c:c + 1])
 
     def step_inputs(self, T, k_rows, v_rows):
         """Consume one chunk of T tokens whose layer inputs the caller has written
-        into self.inputs (q, k, v, g, beta, each [layer][token]...) rows [0, T);
-        replays the captured graph.  Same results as step, bit for bit."""
-        if self.graph is None:
+        into self.inputs (q, k, v, g, beta, each [layer][token]...) rows [0, T).
+        Same results as step, bit for bit."""
+        if self.inputs is None:
             raise RuntimeError("capture_graph() first")
         if not 0 < T <= self.max_chunk:
             raise ValueError(f"chunk of {T} tokens (1..{self.max_chunk})")
-        c = self.n_chunks
-        if c >= self.scores.numel():
+        if self.n_chunks >= self.scores.numel():
             raise ValueError("score table full")
-        self.cu[1:2].fill_(T)
-        self.graphs[min(self.graphs) if T <= min(self.graphs) else self.max_chunk].replay()
-        self.scores[c:c + 1].copy_(self.score_buf)
+        self._layers(T, self.inputs)
         return self._append_and_evict(T, k_rows, v_rows)
 
     def save(self) -> Snapshot:

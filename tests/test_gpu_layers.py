@@ -1,0 +1,113 @@
+"""gdn_layers_fwd (every layer of a chunk in one call, rows at a pitch) against
+one gdn_chunk_fwd call per layer, and gdn_pack_layers against plain copies.
+
+Where both take the per-slice kernel the results are the same bits.  From 64
+heads on the layers take the whole-head kernel, whose operands are rounded to
+fp16 at the same places; o, the states and the drift sums then agree within
+2e-3, the bound both kernels keep against the oracle."""
+import pytest
+import torch
+
+from gpu_helpers import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ds():
+    import paper_2609_27470_amd as ds
+    ds.lib()
+    return ds
+
+
+def layers(L, T, H_k, H_v, d, seed=0):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    rnd = lambda *s: torch.randn(*s, device=DEV, generator=g)  # noqa: E731
+    unit = lambda x: (x / x.norm(dim=-1, keepdim=True)).to(torch.bfloat16)  # noqa: E731
+    return [(unit(rnd(T, H_k, d)), unit(rnd(T, H_k, d)), rnd(T, H_v, d).to(torch.bfloat16),
+             -torch.nn.functional.softplus(rnd(T, H_v)), torch.sigmoid(rnd(T, H_v))) for _ in range(L)]
+
+
+def packed_like(ds, xs, T, pitch):
+    out = tuple(torch.full((len(xs), pitch) + t.shape[1:], 7, dtype=t.dtype, device=DEV) for t in xs[0])
+    ds.gdn_pack_layers(xs, T, out)
+    return out
+
+
+def rel(a, b):
+    return float((a.double() - b.double()).norm() / b.double().norm())
+
+
+@pytest.mark.parametrize("per_slice", [True, False])
+@pytest.mark.parametrize("L,T,pitch,H_k,H_v,d,odt", [
+    (3, 1, 1, 2, 2, 64, torch.float32), (3, 65, 70, 2, 4, 64, torch.bfloat16), (1, 125, 132, 2, 4, 128, torch.float32),
+    (15, 129, 132, 2, 4, 128, torch.bfloat16), (16, 63, 64, 2, 4, 128, torch.float32),
+    (16, 128, 131, 1, 4, 128, torch.bfloat16), (5, 132, 132, 8, 16, 128, torch.float32),
+    (24, 64, 132, 8, 16, 128, torch.bfloat16)])
+def test_layers_match_one_call_per_layer(ds, L, T, pitch, H_k, H_v, d, odt, per_slice):
+    xs = layers(L, T, H_k, H_v, d)
+    S0 = 0.3 * torch.randn(L, 1, H_v, d, d, device=DEV)
+    pairs = H_v * (d // 16) if per_slice else H_v
+    ref_o, ref_S = torch.empty(L, T, H_v, d, dtype=odt, device=DEV), S0.clone()
+    ref_p = torch.empty(L, 1, pairs, 2, device=DEV)
+    for l, x in enumerate(xs):
+        ds.gdn_chunk_fwd(*x, [T], 0, state_in=ref_S[l], state_out=ref_S[l], o=ref_o[l], drift_partials=ref_p[l],
+                         drift_per_slice=per_slice)
+    S, p = S0.clone(), torch.empty_like(ref_p)
+    o = torch.full((L, pitch, H_v, d), 5, dtype=odt, device=DEV)
+    ws = torch.empty(ds.gdn_workspace_bytes(ds.gdn_shape([T] * L, H_k, H_v, d, 0, per_slice)), dtype=torch.uint8, device=DEV)
+    ds.gdn_layers_fwd(*packed_like(ds, xs, T, pitch), T, S, o, p, ws, drift_per_slice=per_slice)
+    torch.cuda.synchronize()
+    if L * H_v < 64 or d == 64:
+        assert torch.equal(o[:, :T], ref_o) and torch.equal(S, ref_S) and torch.equal(p, ref_p)
+    else:
+        assert rel(o[:, :T], ref_o) <= 2e-3 + (4e-3 if odt == torch.bfloat16 else 0)  # a bf16 output's own rounding
+        assert rel(S, ref_S) <= 2e-3 and rel(p, ref_p) <= 2e-3
+    assert bool((o[:, T:] == 5).all())
+
+
+@pytest.mark.parametrize("L,T,pitch,H_k,H_v,d", [(1, 1, 1, 1, 1, 64), (64, 3, 5, 1, 2, 64), (65, 2, 2, 1, 3, 64),
+                                                 (2, 131, 132, 16, 32, 128)])
+def test_pack_copies_every_row_and_no_other(ds, L, T, pitch, H_k, H_v, d):
+    xs = layers(L, T + 1, H_k, H_v, d, seed=1)
+    out = packed_like(ds, xs, T, pitch)
+    torch.cuda.synchronize()
+    for i, t in enumerate(out):
+        assert torch.equal(t[:, :T], torch.stack([x[i][:T] for x in xs]))
+        assert bool((t[:, T:] == 7).all())
+
+
+def test_stream_in_layer_groups(ds, monkeypatch):
+    """A session whose workspace bound splits its layers over several calls gives the same chunks."""
+    from paper_2609_27470_amd import streaming
+    L, H_k, H_v, d = 5, 2, 4, 64
+    new = lambda: streaming.DeltaSStream(L, H_k, H_v, d, 1, 64, 256, 80, 16, 4, 64, 2, device=DEV)  # noqa: E731
+    a = new()
+    monkeypatch.setattr(streaming, "LAYERS_WORKSPACE", ds.gdn_workspace_bytes(ds.gdn_shape([80] * 2, H_k, H_v, d, 0)))
+    b = new()
+    assert a.group == L and b.group == 2
+    rows = torch.zeros(1, 80, 64, dtype=torch.int16, device=DEV)
+    for c, T in enumerate([80, 33, 64]):
+        xs = layers(L, T, H_k, H_v, d, seed=c)
+        for s in (a, b):
+            s.step(xs, rows, rows)
+    assert torch.equal(a.state, b.state) and torch.equal(a.o, b.o) and torch.equal(a.scores[:3], b.scores[:3])
+
+
+def test_refused_arguments(ds):
+    xs = layers(2, 4, 1, 2, 64)
+    packed = packed_like(ds, xs, 4, 4)
+    S, p = torch.zeros(2, 1, 2, 64, 64, device=DEV), torch.zeros(2, 1, 2, 2, device=DEV)
+    o = torch.zeros(2, 4, 2, 64, device=DEV)
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+    with pytest.raises(ds.DeltasError):
+        ds.gdn_layers_fwd(*packed, 5, S, o, p, ws)  # more tokens than the pitch
+    with pytest.raises(ds.DeltasError):
+        ds.gdn_layers_fwd(*packed, 4, S, o, p, ws[:64])
+    with pytest.raises(ValueError):
+        ds.gdn_layers_fwd(*packed, 4, S[:1], o, p, ws)
+    with pytest.raises(ValueError):
+        ds.gdn_pack_layers(xs, 5, packed)
+    with pytest.raises(ValueError):
+        ds.gdn_pack_layers([x[:2] + (x[2][:, :1],) + x[3:] for x in xs], 4, packed)
