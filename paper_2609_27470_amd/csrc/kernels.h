@@ -78,7 +78,7 @@ hipError_t launch_drift(const float *partials, int L, int F, int H_v, int mode, 
 constexpr int KV_MAX_PLANES = 64;  // 2 * n_layers
 
 struct KvWorkspace {
-    size_t offStatus, offPlanes, offKeep, offThRun, offRunStart, offRunKey, offRunBkt, offRunTake, offRunFrom,
+    size_t offStatus, offPlanes, offKeep, offRunStart, offRunKey, offRunBkt, offRunTake, offRunFrom,
         offStage, total;
     size_t stage_bytes;  // staging area of the moves
 };

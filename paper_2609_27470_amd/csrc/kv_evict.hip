@@ -13,9 +13,18 @@
 //   * the leftover budget is filled the same way over all spans from the
 //     tokens not yet kept;
 //   * kept slots -> ascending keep list.
-// Slot data is read in blocks of 4 consecutive slots per thread with one
-// 16-byte load (adjacent lanes read adjacent 16 bytes), 4 Ki slots per
-// block and memory round trip.
+// The runs with their first kept slots are the whole decision: the keep list is
+// the sinks, the tail of every run and the window, written run by run.
+// One workgroup is a serial chain of memory round trips, block-wide scans and
+// vector work, so: slot data is read once, in blocks of 4 consecutive slots per
+// thread with one 16-byte load (adjacent lanes read adjacent 16 bytes), five
+// blocks of 4 Ki slots per round trip and scan (a budget of 16384 tokens and
+// what is above it in one step; more do not fit the registers of 16 waves); a
+// wave whose 256 slots are all candidates skips the tests for the edges; and
+// each run is compared with the others by as many lanes as there are to spare.
+// 16509 slots in 165 runs (indexed) 42 -> 28 us, 8317 in 67 21.4 -> 14.7,
+// 17408 in 17 25 -> 15 (before: blocks one by one, chunk ids read a second time for
+// the keep list, one lane per run).
 // With a slot table (the indexed variant) the K and V rows never move: the
 // select kernel itself compacts pos, chunk_id and slot (the physical row of
 // each logical token) in place and lists the freed physical rows.
@@ -39,9 +48,10 @@
 namespace ds {
 
 constexpr int SEL_THREADS = 1024;
-constexpr int SEL_PER = 4;                          // consecutive slots per thread per pass block
+constexpr int SEL_PER = 4;                          // consecutive slots per thread and block
 constexpr int SEL_BLOCK = SEL_THREADS * SEL_PER;
-static_assert(SEL_PER == 4, "pass 2 stores a thread's four inverse entries as one int4");
+constexpr int SEL_SUB = 5;                          // blocks per step of a pass
+constexpr int SEL_STEP = SEL_SUB * SEL_BLOCK;
 constexpr long long STAGE_AREA = 256ll << 20;       // at most this much staging area for the segments' tails
 
 // pointer into global memory (lets the compiler emit global rather than flat accesses)
@@ -55,7 +65,7 @@ struct KvArgs {
     int num_chunks, len, M, n_s, n_w, N;
     int32_t *status;   // [0] outcome (0 ok, 1 invariants broken, 2 keep count wrong), [1] skip the moves,
                        // [3] first moved slot
-    int32_t *keep, *run_start, *run_bkt, *run_take, *run_from, *th_run;
+    int32_t *keep, *run_start, *run_bkt, *run_take, *run_from;
     unsigned long long *run_key;
     int32_t *keep_out;
     int32_t *slot;      // indexed variant: physical row of each logical token (NULL: gather variant)
@@ -95,24 +105,43 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     return v;
 }
 
-// Exclusive prefix sum over the 1024 threads of the block: a scan inside each
-// wave, then wave 0 scans the 16 wave totals the same way.
-__device__ int block_excl_scan(int x, int *s_tmp, int &total) {
+// Exclusive prefix sums over the 1024 threads of the block, of N values per
+// thread with all of value 0 before value 1 and so on: a scan inside each wave,
+// then wave 0 scans the 16 N wave totals, two per lane.
+template <int N>
+__device__ __forceinline__ void block_excl_scan(int (&x)[N], int *s_tmp, int &total) {
+    constexpr int W = SEL_THREADS / 64;
+    static_assert(N * W <= 128, "two wave totals per lane");
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int incl = wave_incl_scan(x);
-    if (lane == 63) s_tmp[wid] = incl;
-    lds_sync();
-    if (wid == 0) {
-        const int t = lane < SEL_THREADS / 64 ? s_tmp[lane] : 0;
-        const int it = wave_incl_scan(t);
-        if (lane < SEL_THREADS / 64) s_tmp[lane] = it - t;
-        if (lane == SEL_THREADS / 64 - 1) s_tmp[SEL_THREADS / 64] = it;
+    int incl[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) incl[i] = wave_incl_scan(x[i]);
+    if (lane == 63) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) s_tmp[i * W + wid] = incl[i];
     }
     lds_sync();
-    const int res = s_tmp[wid] + incl - x;
-    total = s_tmp[SEL_THREADS / 64];
+    if (wid == 0) {
+        const int e = 2 * lane;
+        const bool in = e < N * W;  // N W is even
+        const int t0 = in ? s_tmp[e] : 0, t1 = in ? s_tmp[e + 1] : 0;
+        const int it = wave_incl_scan(t0 + t1);
+        if (in) {
+            s_tmp[e] = it - t0 - t1;
+            s_tmp[e + 1] = it - t1;
+        }
+        if (lane == 63) s_tmp[N * W] = it;
+    }
     lds_sync();
-    return res;
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = s_tmp[i * W + wid] + incl[i] - x[i];
+    total = s_tmp[N * W];
+    lds_sync();
+}
+__device__ __forceinline__ int block_excl_scan(int x, int *s_tmp, int &total) {
+    int v[1] = {x};
+    block_excl_scan(v, s_tmp, total);
+    return v[0];
 }
 
 // Same DPP pattern with max; lanes without a source contribute -1 (x >= -1).
@@ -151,13 +180,9 @@ __device__ long long block_sum_ll(long long x, long long *s_tmp) {
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
     if (lane == 0) s_tmp[wid] = x;
     lds_sync();
-    if (tid == 0) {
-        long long acc = 0;
-        for (int i = 0; i < SEL_THREADS / 64; ++i) acc += s_tmp[i];
-        s_tmp[SEL_THREADS / 64] = acc;
-    }
-    lds_sync();
-    const long long r = s_tmp[SEL_THREADS / 64];
+    long long r = 0;
+#pragma unroll
+    for (int i = 0; i < SEL_THREADS / 64; ++i) r += s_tmp[i];
     lds_sync();
     return r;
 }
@@ -189,12 +214,12 @@ constexpr int SORT_MIN = 512;  // more runs than this (up to RUN_CAP) are ranked
 
 __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
     __shared__ RunRec s_run[RUN_CAP];
-    __shared__ int s_take[RUN_CAP], s_from[RUN_CAP], s_ord[RUN_CAP];
-    __shared__ int s_keep[SEL_BLOCK], s_free[SEL_BLOCK];  // one pass-2 block's keep entries and freed slots
-    __shared__ int s_scan[SEL_THREADS / 64 + 1];
-    __shared__ long long s_ll[SEL_THREADS / 64 + 1];
+    __shared__ int s_start[RUN_CAP], s_take[RUN_CAP], s_from[RUN_CAP], s_ord[RUN_CAP];
+    __shared__ int s_keep[SEL_STEP];  // a copy of the keep list's first entries for the indexed variant's move
+    __shared__ int s_scan[SEL_SUB * (SEL_THREADS / 64) + 1];
+    __shared__ long long s_ll[SEL_THREADS / 64];
     __shared__ int s_bad;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     if (tid == 0) {
         a.status[0] = 0;
@@ -202,63 +227,70 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         a.status[2] = 0;
         s_bad = 0;
     }
-    // copy of the plane table with constant indices (no dynamic indexing of
-    // the kernel-argument array)
-#pragma unroll
-    for (int p = 0; p < KV_MAX_PLANES; ++p)
-        if (p == tid && p < a.n_planes) a.plane_tab[p] = a.planes[p];
+    if (tid < a.n_planes) a.plane_tab[tid] = a.planes[tid];
 
     const int c0 = a.n_s, c1 = a.len - a.n_w;
 
     // ---- pass 1: cache invariants and runs of equal chunk id among the
-    // candidates [c0, c1); th_run[block][thread] = runs starting before the
-    // thread's slots
+    // candidates [c0, c1)
     int R = 0;
-    // the next block's entries are loaded while this one is scanned
-    int nch[SEL_PER], nps[SEL_PER], npc = -1, npp = 0;
-    auto fetch1 = [&](int base) {
-        const int lo = base + tid * SEL_PER;
-        load_block(a.chunk, lo, a.len, nch);
-        load_block(a.pos, lo, a.len, nps);
-        const bool has_prev = lo > 0 && lo <= a.len;
-        npc = has_prev ? a.chunk[lo - 1] : -1;
-        npp = has_prev ? a.pos[lo - 1] : 0;
-    };
-    if (a.len > 0) fetch1(0);
-    for (int base = 0; base < a.len; base += SEL_BLOCK) {
-        const int lo = base + tid * SEL_PER;
-        int ch[SEL_PER], ps[SEL_PER];
+    for (int base = 0; base < a.len; base += SEL_STEP) {
+        int ch[SEL_SUB][SEL_PER], ps[SEL_SUB][SEL_PER], pc0[SEL_SUB], pp0[SEL_SUB], off[SEL_SUB];
 #pragma unroll
-        for (int k = 0; k < SEL_PER; ++k) {
-            ch[k] = nch[k];
-            ps[k] = nps[k];
+        for (int u = 0; u < SEL_SUB; ++u) {
+            const int lo = base + u * SEL_BLOCK + tid * SEL_PER;
+            load_block(a.chunk, lo, a.len, ch[u]);
+            load_block(a.pos, lo, a.len, ps[u]);
+            const bool has_prev = lo > 0 && lo <= a.len;
+            pc0[u] = has_prev ? a.chunk[lo - 1] : -1;
+            pp0[u] = has_prev ? a.pos[lo - 1] : 0;
         }
-        const int pc0 = npc;
-        int pc = pc0, pp = npp;
-        if (base + SEL_BLOCK < a.len) fetch1(base + SEL_BLOCK);
-        int bad = 0, cnt = 0;
+        int bad = 0;
+        unsigned starts[SEL_SUB];  // the slots of the thread's four at which a run starts
 #pragma unroll
-        for (int k = 0; k < SEL_PER; ++k) {
-            const int i = lo + k;
-            if (i < a.len) {
-                if (ch[k] < 0 || ch[k] >= a.num_chunks) bad = 1;
-                if (i > 0 && (ch[k] < pc || ps[k] <= pp)) bad = 1;
-                if (i >= c0 && i < c1 && (i == c0 || ch[k] != pc)) ++cnt;
-                pc = ch[k];
-                pp = ps[k];
+        for (int u = 0; u < SEL_SUB; ++u) {
+            const int lo = base + u * SEL_BLOCK + tid * SEL_PER, wlo = base + u * SEL_BLOCK + wid * 64 * SEL_PER;
+            int pc = pc0[u], pp = pp0[u];
+            starts[u] = 0;
+            if (wlo > c0 && wlo + 64 * SEL_PER <= c1) {  // every slot of the wave is a candidate, and not the first
+#pragma unroll
+                for (int k = 0; k < SEL_PER; ++k) {
+                    bad |= ((unsigned)ch[u][k] >= (unsigned)a.num_chunks) | (ch[u][k] < pc) | (ps[u][k] <= pp);
+                    starts[u] |= (unsigned)(ch[u][k] != pc) << k;
+                    pc = ch[u][k];
+                    pp = ps[u][k];
+                }
+            } else if (wlo < a.len) {
+#pragma unroll
+                for (int k = 0; k < SEL_PER; ++k) {
+                    const int i = lo + k;
+                    if (i < a.len) {
+                        if (ch[u][k] < 0 || ch[u][k] >= a.num_chunks) bad = 1;
+                        if (i > 0 && (ch[u][k] < pc || ps[u][k] <= pp)) bad = 1;
+                        if (i >= c0 && i < c1 && (i == c0 || ch[u][k] != pc)) starts[u] |= 1u << k;
+                        pc = ch[u][k];
+                        pp = ps[u][k];
+                    }
+                }
             }
+            off[u] = __popc(starts[u]);
         }
         if (bad) atomicOr(&s_bad, 1);
         int tot = 0;
-        int off = R + block_excl_scan(cnt, s_scan, tot);
-        a.th_run[base / SEL_PER + tid] = off;
-        pc = pc0;
+        block_excl_scan(off, s_scan, tot);
 #pragma unroll
-        for (int k = 0; k < SEL_PER; ++k) {
-            const int i = lo + k;
-            if (i < a.len) {
-                if (i >= c0 && i < c1 && (i == c0 || ch[k] != pc)) a.run_start[off++] = i;
-                pc = ch[k];
+        for (int u = 0; u < SEL_SUB; ++u) {
+            int r = R + off[u];
+#pragma unroll
+            for (int k = 0; k < SEL_PER; ++k) {
+                if (starts[u] & (1u << k)) {
+                    const int i = base + u * SEL_BLOCK + tid * SEL_PER + k;
+                    if (r < RUN_CAP) {  // the run's first slot and chunk, for the keys
+                        s_start[r] = i;
+                        s_ord[r] = ch[u][k];
+                    }
+                    a.run_start[r++] = i;
+                }
             }
         }
         R += tot;
@@ -285,8 +317,9 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
     const int N = max(1, a.N);
     const bool in_lds = R <= RUN_CAP;
     for (int r = tid; r < R; r += SEL_THREADS) {
-        const int rs = a.run_start[r], re = a.run_start[r + 1];
-        const int chn = a.chunk[rs];
+        const int rs = in_lds ? s_start[r] : a.run_start[r];
+        const int re = in_lds ? (r + 1 < R ? s_start[r + 1] : c1) : a.run_start[r + 1];
+        const int chn = in_lds ? s_ord[r] : a.chunk[rs];
         const unsigned long long key = ((unsigned long long)orderable(a.scores[chn]) << 32) | (unsigned)chn;
         const int bkt = (int)(((long long)N * (chn - a_min)) / span);
         a.run_key[r] = key;
@@ -320,6 +353,15 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
                 }
                 lds_sync();
             }
+    };
+    // up to SORT_MIN runs: lanes per run in the pairwise comparisons (a power of
+    // two, at most a wave), run and place among them of this lane
+    int G = 1;
+    while (G < 64 && 2 * G * R <= SEL_THREADS) G <<= 1;
+    const int gr = tid / G, gi = tid % G;
+    auto group_sum = [&](int x) {
+        for (int off = 1; off < G; off <<= 1) x += __shfl_xor(x, off, 64);
+        return x;
     };
     // sorted positions 2 tid and 2 tid + 1 (Rp <= 2 SEL_THREADS); -1 past R
     const int i0 = 2 * tid, i1 = i0 + 1;
@@ -355,37 +397,36 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
             a.run_take[r1] = t;
             taken += t;
         }
+    } else if (in_lds) {
+        int above = 0;
+        const RunRec me = s_run[max(0, min(gr, R - 1))];
+        // eight records read before they are compared: one LDS round trip per
+        // eight runs rather than per run
+        for (int r2 = gi; r2 < R; r2 += 8 * G) {
+            RunRec o[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o[q] = s_run[min(r2 + q * G, R - 1)];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (r2 + q * G < R && o[q].bkt == me.bkt && o[q].key > me.key) above += o[q].len;
+        }
+        above = group_sum(above);
+        if (gr < R && gi == 0) {
+            const int t = (int)min((long long)me.len, max(0LL, quota - above));
+            a.run_take[gr] = t;
+            s_take[gr] = t;
+            taken = t;
+        }
     } else {
         for (int r = tid; r < R; r += SEL_THREADS) {
-            long long above = 0, ln;
-            if (in_lds) {
-                const RunRec me = s_run[r];
-                ln = me.len;
-                // eight records read before they are compared: one LDS round
-                // trip per eight runs rather than per run
-                int r2 = 0;
-                for (; r2 + 8 <= R; r2 += 8) {
-                    RunRec o[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) o[q] = s_run[r2 + q];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        if (o[q].bkt == me.bkt && o[q].key > me.key) above += o[q].len;
-                }
-                for (; r2 < R; ++r2) {
-                    const RunRec o = s_run[r2];
-                    if (o.bkt == me.bkt && o.key > me.key) above += o.len;
-                }
-            } else {
-                const unsigned long long key = a.run_key[r];
-                const int bk = a.run_bkt[r];
-                ln = a.run_start[r + 1] - a.run_start[r];
-                for (int r2 = 0; r2 < R; ++r2)
-                    if (a.run_bkt[r2] == bk && a.run_key[r2] > key) above += a.run_start[r2 + 1] - a.run_start[r2];
-            }
+            const unsigned long long key = a.run_key[r];
+            const int bk = a.run_bkt[r];
+            const long long ln = a.run_start[r + 1] - a.run_start[r];
+            long long above = 0;
+            for (int r2 = 0; r2 < R; ++r2)
+                if (a.run_bkt[r2] == bk && a.run_key[r2] > key) above += a.run_start[r2 + 1] - a.run_start[r2];
             const long long t = min(ln, max(0LL, quota - above));
             a.run_take[r] = (int)t;
-            if (in_lds) s_take[r] = (int)t;
             taken += t;
         }
     }
@@ -410,133 +451,88 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         const int m0 = r0 >= 0 ? s_run[r0].len - t0 : 0, m1 = r1 >= 0 ? s_run[r1].len - t1 : 0;
         const int f0 = block_excl_scan(m0 + m1, s_scan, tot), f1 = f0 + m0;  // left in better runs
         if (r0 >= 0) {
-            const int from = a.run_start[r0 + 1] - (t0 + (int)min((long long)m0, max(0LL, fill - f0)));
+            const int from = s_start[r0] + s_run[r0].len - (t0 + (int)min((long long)m0, max(0LL, fill - f0)));
             a.run_from[r0] = from;
             s_from[r0] = from;
         }
         if (r1 >= 0) {
-            const int from = a.run_start[r1 + 1] - (t1 + (int)min((long long)m1, max(0LL, fill - f1)));
+            const int from = s_start[r1] + s_run[r1].len - (t1 + (int)min((long long)m1, max(0LL, fill - f1)));
             a.run_from[r1] = from;
             s_from[r1] = from;
         }
+    } else if (in_lds) {
+        int above = 0;
+        const RunRec me = s_run[max(0, min(gr, R - 1))];
+        for (int r2 = gi; r2 < R; r2 += 8 * G) {
+            RunRec o[8];
+            int tq[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                o[q] = s_run[min(r2 + q * G, R - 1)];
+                tq[q] = s_take[min(r2 + q * G, R - 1)];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (r2 + q * G < R && o[q].key > me.key) above += o[q].len - tq[q];
+        }
+        above = group_sum(above);
+        if (gr < R && gi == 0) {
+            const int tk = s_take[gr];
+            const int from = s_start[gr] + me.len - (tk + (int)min((long long)(me.len - tk), max(0LL, fill - above)));
+            a.run_from[gr] = from;
+            s_from[gr] = from;
+        }
     } else {
         for (int r = tid; r < R; r += SEL_THREADS) {
-            long long above = 0, ln, tk;
-            if (in_lds) {
-                const RunRec me = s_run[r];
-                ln = me.len;
-                tk = s_take[r];
-                int r2 = 0;
-                for (; r2 + 8 <= R; r2 += 8) {
-                    RunRec o[8];
-                    int tq[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        o[q] = s_run[r2 + q];
-                        tq[q] = s_take[r2 + q];
-                    }
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        if (o[q].key > me.key) above += o[q].len - tq[q];
-                }
-                for (; r2 < R; ++r2) {
-                    const RunRec o = s_run[r2];
-                    if (o.key > me.key) above += o.len - s_take[r2];
-                }
-            } else {
-                const unsigned long long key = a.run_key[r];
-                ln = a.run_start[r + 1] - a.run_start[r];
-                tk = a.run_take[r];
-                for (int r2 = 0; r2 < R; ++r2)
-                    if (a.run_key[r2] > key) above += (a.run_start[r2 + 1] - a.run_start[r2]) - a.run_take[r2];
-            }
-            const long long f = min(ln - tk, max(0LL, fill - above));
-            const int from = a.run_start[r + 1] - (int)(tk + f);
-            a.run_from[r] = from;
-            if (in_lds) s_from[r] = from;
+            const unsigned long long key = a.run_key[r];
+            const long long ln = a.run_start[r + 1] - a.run_start[r], tk = a.run_take[r];
+            long long above = 0;
+            for (int r2 = 0; r2 < R; ++r2)
+                if (a.run_key[r2] > key) above += (a.run_start[r2 + 1] - a.run_start[r2]) - a.run_take[r2];
+            a.run_from[r] = a.run_start[r + 1] - (int)(tk + min(ln - tk, max(0LL, fill - above)));
         }
     }
     __syncthreads();
+    auto run_start = [&](int r) { return in_lds ? (r < R ? s_start[r] : c1) : a.run_start[r]; };
     auto run_from = [&](int r) { return in_lds ? s_from[r] : a.run_from[r]; };
 
-    // ---- pass 2: keep list (ascending)
-    int total_kept = 0;
+    // ---- keep list (ascending) and, indexed, the freed slots: the sinks, of
+    // every run the slots from run_from on (those before it are evicted), the
+    // window.  A wave writes a run, or several waves one where the runs are few.
+    int total_kept = c0;
     int first_move = a.M;  // smallest destination d with keep[d] != d
     const int n_evict = a.len - a.M;
-    // the next block's entries are loaded while this one is processed
-    int n2ch[SEL_PER], n2sl[SEL_PER], n2pc = -1, n2r = -1;
-    auto fetch2 = [&](int base) {
-        const int lo = base + tid * SEL_PER;
-        load_block(a.chunk, lo, a.len, n2ch);
-        if (a.slot) load_block(a.slot, lo, a.len, n2sl);
-        n2pc = (lo > 0 && lo <= a.len) ? a.chunk[lo - 1] : -1;
-        n2r = (lo < a.len) ? a.th_run[base / SEL_PER + tid] - 1 : -1;  // run holding the slot before lo
+    auto put = [&](int d, int i) __attribute__((always_inline)) {
+        if (d >= a.M) return;
+        a.keep[d] = i;
+        if (a.keep_out) a.keep_out[d] = i;
+        if (d < SEL_STEP) s_keep[d] = i;
     };
-    if (a.len > 0) fetch2(0);
-    for (int base = 0; base < a.len; base += SEL_BLOCK) {
-        const int lo = base + tid * SEL_PER;
-        int ch[SEL_PER], sl[SEL_PER];
-#pragma unroll
-        for (int k = 0; k < SEL_PER; ++k) {
-            ch[k] = n2ch[k];
-            sl[k] = n2sl[k];
-        }
-        int pc = n2pc;
-        int r = n2r;
-        if (base + SEL_BLOCK < a.len) fetch2(base + SEL_BLOCK);
-        int from = (r >= 0 && r < R) ? run_from(r) : 0;
-        unsigned mask = 0;
-#pragma unroll
-        for (int k = 0; k < SEL_PER; ++k) {
-            const int i = lo + k;
-            if (i < a.len) {
-                bool kept = true;
-                if (i >= c0 && i < c1) {
-                    if (i == c0 || ch[k] != pc) {
-                        ++r;
-                        from = run_from(r);
-                    }
-                    kept = i >= from;
-                }
-                if (kept) mask |= 1u << k;
-                pc = ch[k];
-            }
-        }
-        // the block's keep entries and freed slots are collected in LDS and
-        // leave as contiguous stores (scattered 4-byte stores would load the
-        // memory pipeline)
+    for (int i = tid; i < c0; i += SEL_THREADS) put(i, i);
+    for (int rb = 0; rb < R; rb += SEL_THREADS) {
+        const int r = rb + tid, n = min(R - rb, SEL_THREADS);
+        const int from = r < R ? run_from(r) : 0, kept = r < R ? run_start(r + 1) - from : 0;
         int tot = 0;
-        int off = total_kept + block_excl_scan(__popc(mask), s_scan, tot);
-        const int ev_base = base - total_kept;  // tokens evicted before this block
-#pragma unroll
-        for (int k = 0; k < SEL_PER; ++k) {
-            const int i = lo + k;
-            if (i < a.len) {
-                if (mask & (1u << k)) {
-                    if (off < a.M) {
-                        s_keep[off - total_kept] = i;
-                        if (off != i) first_move = min(first_move, off);
-                    }
-                    ++off;
-                } else if (a.slot) {
-                    // evicted token i is the (i - off)-th evicted one in logical order
-                    s_free[i - off - ev_base] = sl[k];
-                }
-            }
-        }
+        const int dst = total_kept + block_excl_scan(kept, s_scan, tot);
+        if (kept > 0 && from != dst) first_move = min(first_move, dst);
+        s_ord[tid] = dst;
         lds_sync();
-        const int kn = min(tot, a.M - total_kept);
-        for (int q = tid; q < kn; q += SEL_THREADS) {
-            a.keep[total_kept + q] = s_keep[q];
-            if (a.keep_out) a.keep_out[total_kept + q] = s_keep[q];
-        }
-        if (a.slot) {
-            const int fn = min(min(a.len - base, SEL_BLOCK) - tot, n_evict - ev_base);
-            for (int q = tid; q < fn; q += SEL_THREADS) a.free_out[ev_base + q] = s_free[q];
+        constexpr int W = SEL_THREADS / 64;
+        const int per = max(1, W / n), lane = tid & 63, i0 = wid % per * 64 + lane, step = 64 * per;
+        for (int q = wid / per; q < n; q += W / per) {
+            const int to = s_ord[q], st = run_start(rb + q), fr = run_from(rb + q), en = run_start(rb + q + 1);
+            for (int i = fr + i0; i < en; i += step) put(to + i - fr, i);
+            if (a.slot) {  // st - to tokens were evicted before this run
+                for (int i = st + i0; i < fr; i += step)
+                    if (i - to < n_evict) a.free_out[i - to] = a.slot[i];
+            }
         }
         lds_sync();
         total_kept += tot;
     }
+    for (int i = tid; i < a.n_w; i += SEL_THREADS) put(total_kept + i, c1 + i);
+    if (a.n_w > 0 && c1 != total_kept) first_move = min(first_move, total_kept);
+    total_kept += a.n_w;
     // ---- moving destinations form the suffix [first_move, M) (keep[d] - d is
     // nondecreasing)
     {
@@ -566,28 +562,15 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
     // next block's reads lie above what this block writes.
     if (a.slot && total_kept == a.M) {
         __syncthreads();  // the keep list written above by every thread is read below
-        // the keep entries of the next block are loaded while this block moves
-        // (the pass never writes the keep list): one dependent round trip to
-        // memory per block instead of two
-        int nk[SEL_PER];
-        auto fetch_keep = [&](int base) __attribute__((always_inline)) {
+        const bool one = a.M <= SEL_STEP;  // the whole keep list is in LDS
+        constexpr int PER = SEL_STEP / SEL_THREADS;
+        for (int base = first_move; base < a.M; base += SEL_STEP) {
+            int vp[PER], vc[PER], vs[PER];
 #pragma unroll
-            for (int k = 0; k < SEL_PER; ++k) {
-                const int d = base + k * SEL_THREADS + tid;
-                nk[k] = d < a.M ? a.keep[d] : 0;
-            }
-        };
-        if (first_move < a.M) fetch_keep(first_move);
-        for (int base = first_move; base < a.M; base += SEL_BLOCK) {
-            int vp[SEL_PER], vc[SEL_PER], vs[SEL_PER], kk[SEL_PER];
-#pragma unroll
-            for (int k = 0; k < SEL_PER; ++k) kk[k] = nk[k];
-            if (base + SEL_BLOCK < a.M) fetch_keep(base + SEL_BLOCK);
-#pragma unroll
-            for (int k = 0; k < SEL_PER; ++k) {
+            for (int k = 0; k < PER; ++k) {
                 const int d = base + k * SEL_THREADS + tid;
                 if (d < a.M) {
-                    const int src = kk[k];
+                    const int src = one ? s_keep[d] : a.keep[d];
                     vp[k] = a.pos[src];
                     vc[k] = a.chunk[src];
                     vs[k] = a.slot[src];
@@ -595,7 +578,7 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
             }
             __syncthreads();
 #pragma unroll
-            for (int k = 0; k < SEL_PER; ++k) {
+            for (int k = 0; k < PER; ++k) {
                 const int d = base + k * SEL_THREADS + tid;
                 if (d < a.M) {
                     a.pos[d] = vp[k];
@@ -822,7 +805,6 @@ hipError_t kv_noalloc_scratch(char **out) {
 KvWorkspace kv_workspace_layout(int n_layers, int row_bytes, int capacity) {
     KvWorkspace w{};
     const size_t cap = (size_t)capacity;
-    const size_t blocks = (cap + SEL_BLOCK - 1) / SEL_BLOCK;
     size_t off = 0;
     w.offStatus = off;
     off = align256(off + 64);
@@ -830,8 +812,6 @@ KvWorkspace kv_workspace_layout(int n_layers, int row_bytes, int capacity) {
     off = align256(off + KV_MAX_PLANES * sizeof(char *));
     w.offKeep = off;
     off = align256(off + cap * 4);
-    w.offThRun = off;
-    off = align256(off + blocks * SEL_THREADS * 4);
     w.offRunStart = off;
     off = align256(off + (cap + 1) * 4);
     w.offRunKey = off;
@@ -898,7 +878,6 @@ hipError_t launch_kv_evict(const KvLaunch &p, hipStream_t stream) {
     a.N = p.n_buckets;
     a.status = (int32_t *)(ws + p.lay.offStatus);
     a.keep = (int32_t *)(ws + p.lay.offKeep);
-    a.th_run = (int32_t *)(ws + p.lay.offThRun);
     a.run_start = (int32_t *)(ws + p.lay.offRunStart);
     a.run_key = (unsigned long long *)(ws + p.lay.offRunKey);
     a.run_bkt = (int32_t *)(ws + p.lay.offRunBkt);

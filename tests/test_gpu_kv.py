@@ -416,3 +416,20 @@ def test_many_strips_of_wide_rows(ds):
     chunk = np.repeat(np.arange(5), 60).astype(np.int32)
     scores = np.array([0.1, 1, 1, 1, 1], np.float32)
     one_event(ds, 1, 32768, chunk, np.arange(300, dtype=np.int32), scores, 240, 0, 0, 1)
+
+
+@pytest.mark.parametrize("n,runs,M,ns,nw,nb", [
+    (20480, 1, 20479, 0, 0, 1), (20481, 2, 20480, 4, 255, 2), (20479, 15, 16384, 0, 0, 4), (24577, 16, 20481, 256, 256, 1),
+    (41000, 17, 30000, 5, 1023, 3), (4096, 31, 1, 0, 0, 1), (4097, 64, 4096, 3, 1, 5), (6000, 127, 5000, 0, 100, 2),
+    (9000, 511, 8000, 1, 0, 4), (9000, 512, 4000, 0, 7, 1), (9000, 513, 4000, 7, 0, 7), (300, 300, 150, 0, 0, 1),
+    (1024, 1, 600, 300, 300, 1)])
+def test_selection_edges(ds, n, runs, M, ns, nw, nb):
+    """Lengths around a step of the selection (20480 slots), run counts around a run per wave, the lanes that share a
+    run's comparisons and the sorted ranking (from 513 on), budgets within and beyond the copy of the keep list."""
+    rng = np.random.default_rng(n + runs)
+    cuts = np.sort(rng.choice(np.arange(1, n), runs - 1, replace=False))
+    chunk = np.searchsorted(cuts, np.arange(n), side="right").astype(np.int32)
+    pos = np.cumsum(rng.integers(1, 4, n)).astype(np.int32)
+    scores = rng.choice([0.1, 0.2, 0.5, 1.0, np.inf], size=runs).astype(np.float32)
+    one_event(ds, 1, 8, chunk, pos, scores, M, ns, nw, nb)
+    indexed_event(ds, chunk, pos, scores, M, ns, nw, nb, seed=2)
