@@ -21,7 +21,7 @@ copies are plain device copies.
 A chunk is a tiny call per layer (about 125 tokens) that leaves most of the GPU
 idle, and the inputs of all layers are there before the first one runs: the
 layers go through `gdn_layers_fwd` together (24 layers x 125 tokens x 32 heads,
-append and eviction included: 142 us a chunk; with a launch per layer, replayed
+append and eviction included: 127 us a chunk; with a launch per layer, replayed
 as a HIP graph, 434 us).
 `capture_graph` allocates input buffers in that call's layout (`inputs`);
 `step_inputs` runs a chunk that the caller has written there, `step` first
@@ -135,6 +135,8 @@ class DeltaSStream:
             self.kv_ws = torch.empty(max(kv_indexed_workspace_bytes(self.capacity), 1), dtype=torch.uint8, device=dev)
         else:
             self.slot = None
+            self._rows = torch.arange(self.capacity, dtype=torch.int32, device=dev)
+            self._slots = torch.empty(self.capacity, dtype=torch.int32, device=dev)   # written, never read
             self.kv_ws = torch.empty(max(kv_workspace_bytes(kv_layers, row_elems * 2, self.capacity), 1),
                                      dtype=torch.uint8, device=dev)
         self.kv_fail = torch.zeros(1, dtype=torch.int32, device=dev)   # max outcome word of every eviction
@@ -192,6 +194,14 @@ class DeltaSStream:
             raise EvictionFailed(f"an eviction reported outcome {code} (1: cache invariants broken, "
                                  "2: keep count wrong, 3: gather wait timed out)")
 
+    def _appendable(self, rows, T):
+        """Whether kv_append_indexed can read the chunk's rows as they are (other types, layouts and devices go
+        through copies)."""
+        row = self.k.shape[2]
+        return (rows.dtype == self.k.dtype and rows.device == self.k.device and rows.shape == (self.k.shape[0], T, row)
+                and rows.stride(2) == 1 and rows.stride(1) == row and rows.data_ptr() % 16 == 0
+                and rows.stride(0) % 8 == 0 and row % 8 == 0 and row <= 32768 and 0 < rows.shape[0] <= 32)
+
     def _append_and_evict(self, T, k_rows, v_rows):
         c = self.n_chunks
         n = self.length
@@ -200,6 +210,9 @@ class DeltaSStream:
             kv_append_indexed(self.k, self.v, k_rows, v_rows, self._free_bufs[self._fa], self._na, self.freed,
                               self._nb, rest, T, n, self.next_pos, c, self.pos, self.chunk_id, self.slot)
             self._fa, self._na, self._nb = 1 - self._fa, self._na + self._nb - T, 0
+        elif self._appendable(k_rows, T) and self._appendable(v_rows, T):   # the same launch, token i in row i
+            kv_append_indexed(self.k, self.v, k_rows, v_rows, self._rows[n:], T, None, 0, None, T, n, self.next_pos, c,
+                              self.pos, self.chunk_id, self._slots)
         else:
             self.k[:, n:n + T].copy_(k_rows)
             self.v[:, n:n + T].copy_(v_rows)

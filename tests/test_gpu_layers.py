@@ -111,3 +111,27 @@ def test_refused_arguments(ds):
         ds.gdn_pack_layers(xs, 5, packed)
     with pytest.raises(ValueError):
         ds.gdn_pack_layers([x[:2] + (x[2][:, :1],) + x[3:] for x in xs], 4, packed)
+
+
+@pytest.mark.parametrize("form", ["contiguous", "slice", "strided", "host", "misaligned"])
+def test_rows_of_every_layout_join_the_contiguous_cache(ds, form):
+    """The compacted cache takes a chunk's rows in one launch where it can read them as they are, else by copies."""
+    from paper_2609_27470_amd.streaming import DeltaSStream
+    KL, row, T = 2, 64, 40
+    s = DeltaSStream(2, 1, 2, 64, KL, row, 200, 64, 16, 4, 32, 2, device=DEV, indexed=False)
+    want = torch.empty(KL, 0, row, dtype=torch.int16, device=DEV)
+    for c in range(4):
+        rows = torch.randint(-999, 999, (KL, T, row), dtype=torch.int16, device=DEV)
+        want = torch.cat([want, rows], 1)
+        if form == "slice":
+            rows = torch.cat([rows, rows], 1)[:, :T]
+        elif form == "strided":
+            rows = rows.transpose(0, 1).contiguous().transpose(0, 1)
+        elif form == "host":
+            rows = rows.cpu()
+        elif form == "misaligned":
+            rows = torch.cat([torch.zeros(1, dtype=torch.int16, device=DEV), rows.flatten()])[1:].view(KL, T, row)
+        s.step(layers(2, T, 1, 2, 64, seed=c), rows, rows)
+    n = 4 * T
+    assert s.length == n and torch.equal(s.k[:, :n], want) and torch.equal(s.v[:, :n], want)
+    assert s.pos[:n].tolist() == list(range(n)) and s.chunk_id[:n].tolist() == [i // T for i in range(n)]
