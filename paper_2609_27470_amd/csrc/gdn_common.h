@@ -55,6 +55,12 @@ struct GdnArgs {
 // Global tile index -> (stream, first token, valid tokens).  Tiles are
 // numbered stream by stream; a stream of n tokens has ceil(n / 64) tiles.
 __device__ bool locate_tile(const Streams &s, int ti, int &t0, int &n) {
+    if (s.T < 0) {  // at a pitch
+        const int nt = (TILE - 1 - s.T) / TILE, b = ti / nt, lt = ti - b * nt;
+        t0 = b * (int)(uintptr_t)s.cu + TILE * lt;
+        n = min(TILE, -s.T - TILE * lt);
+        return b < s.B;
+    }
     int base = 0;
     bool found = false;
     for_streams(s, [&](int, int st, int en) {

@@ -63,10 +63,13 @@ __device__ __forceinline__ void drift_setup(const GdnArgs &a, int tid, int nt) {
     if (a.drift_out)
         for (int i = tid; i < a.st.B * a.H_v; i += nt) a.drift_cnt[i] = 0u;
     int real = 0;
-    for_streams(a.st, [&](int, int s0, int e0) {
-        real += frames_in(e0 - s0, a.frame_len);
-        return false;
-    });
+    if (a.st.T < 0)
+        real = a.st.B * frames_in(-a.st.T, a.frame_len);
+    else
+        for_streams(a.st, [&](int, int s0, int e0) {
+            real += frames_in(e0 - s0, a.frame_len);
+            return false;
+        });
     const int per = a.drift_zero_per_frame;
     for (int i = min(real, a.n_frames) * per + tid; i < a.n_frames * per; i += nt)
         *(float2 *)(a.drift_zero + 2 * (size_t)i) = float2{0.f, 0.f};
@@ -538,17 +541,8 @@ __global__ __launch_bounds__(512, 1) void gdn_seq_kernel(GdnArgs a) {
     const int j = qh * a.group + mem / a.n_split, sl = mem % a.n_split;
     const int v0 = 16 * sl;
 
-    int st = 0, en = 0, tile_base = 0, frame_base = 0;
-    for_streams(a.st, [&](int bb, int s0, int e0) {
-        if (bb == b) {
-            st = s0;
-            en = e0;
-            return true;
-        }
-        tile_base += (e0 - s0 + TILE - 1) / TILE;
-        frame_base += frames_in(e0 - s0, a.frame_len);
-        return false;
-    });
+    int st, en, tile_base, frame_base;
+    locate_stream(a.st, b, a.frame_len, st, en, tile_base, frame_base);
     const int len = en - st;
     const int n_tiles = (len + TILE - 1) / TILE;
 

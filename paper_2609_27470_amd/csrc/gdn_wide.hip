@@ -140,17 +140,8 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
     const int r0 = 64 * (mem % HW);  // first state row of this workgroup
     const int sl0 = r0 / 16;          // its first 16-row slice
 
-    int st = 0, en = 0, tile_base = 0, frame_base = 0;
-    for_streams(a.st, [&](int bb, int s0, int e0) {
-        if (bb == b) {
-            st = s0;
-            en = e0;
-            return true;
-        }
-        tile_base += (e0 - s0 + TILE - 1) / TILE;
-        frame_base += frames_in(e0 - s0, a.frame_len);
-        return false;
-    });
+    int st, en, tile_base, frame_base;
+    locate_stream(a.st, b, a.frame_len, st, en, tile_base, frame_base);
     const int len = en - st;
     const int n_tiles = (len + TILE - 1) / TILE;
     // the tiles of this launch: all of them, or those before (wide_phase 1) or
