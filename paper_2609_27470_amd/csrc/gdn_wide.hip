@@ -28,7 +28,11 @@
 // formed from them during the rest of the tile).  The state at a frame's
 // start, needed for ||S_end - S_start||^2, is kept in a scratch area of the
 // workspace (64 KiB per head) rather than in registers, and read back at the
-// frame's end.
+// frame's end; for the first frame of a launch it is read from state_in again (an
+// empty buffer, which reads as zeros, without one), and nothing is kept once no
+// frame follows.  (The copies were a third of the traffic of a short call: one chunk
+// of 125 tokens through 24 layers of 32 heads, with its append and eviction, 127 ->
+// 115 us.)
 //
 // A call of streams of unequal length leaves most CUs idle once the shorter
 // streams end, and the per-tile time of the heads still running is then set
@@ -201,8 +205,8 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
                 for (int kb = 0; kb < NKB; ++kb)
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, S[sl][kb]), rstart, lane16, start_const(sl, kb), 0);
         };
-        if (DRIFT) save_start();
         int frame = frame_base + (a.frame_len > 0 ? tok0 / a.frame_len : 0);
+        bool first = true;  // in the launch's first frame
         int frame_end = a.frame_len > 0 ? min(tok0 + a.frame_len, len) : len;  // tokens done at the next frame end
 
         // The tile runs as software-pipelined regions: every LDS operand is read
@@ -470,12 +474,19 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
             // frame end: per-lane drift sums of the wave's slices against the state the
             // frame started from (read back from the scratch area), snapshot
             if (DRIFT && TILE * lt + n == frame_end) {
+                // (one path for both sources: two of them cost registers in the tile loop)
+                const float *from = first ? (a.state_in ? a.state_in + hbase : nullptr)
+                                          : a.wsStart + (((size_t)b * a.H_v + j) * 8 + wr0 / 16) * NKB * 64 * 4;
+                const __amdgpu_buffer_rsrc_t rfrom = __builtin_amdgcn_make_buffer_rsrc(
+                    (void *)from, (short)0, first ? (a.state_in ? D * D * 4 : 0) : NSL * NKB * 64 * 16, RSRC_FLAGS);
+                const uint32_t lane_from = first ? lane_row : lane16;
 #pragma unroll
                 for (int sl = 0; sl < NSL; ++sl) {
                     float num = 0.f, den = 0.f;
 #pragma unroll
                     for (int kb = 0; kb < NKB; ++kb) {
-                        const f32x4 s0 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rstart, lane16, start_const(sl, kb), 0));
+                        const int at = first ? sconst(sl, kb) : start_const(sl, kb);
+                        const f32x4 s0 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rfrom, lane_from, at, 0));
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float dl = S[sl][kb][e] - s0[e];
@@ -494,7 +505,8 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
                         for (int kb = 0; kb < NKB; ++kb)
                             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, S[sl][kb]), rsn, lane_row, sconst(sl, kb), 0);
                 }
-                save_start();
+                if (lt + 1 < lt1) save_start();
+                first = false;
                 ++frame;
                 frame_end = min(frame_end + a.frame_len, len);
             }

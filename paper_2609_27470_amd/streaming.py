@@ -21,7 +21,7 @@ copies are plain device copies.
 A chunk is a tiny call per layer (about 125 tokens) that leaves most of the GPU
 idle, and the inputs of all layers are there before the first one runs: the
 layers go through `gdn_layers_fwd` together (24 layers x 125 tokens x 32 heads,
-append and eviction included: 127 us a chunk; with a launch per layer, replayed
+append and eviction included: 115 us a chunk; with a launch per layer, replayed
 as a HIP graph, 434 us).
 `capture_graph` allocates input buffers in that call's layout (`inputs`);
 `step_inputs` runs a chunk that the caller has written there, `step` first
