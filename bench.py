@@ -240,7 +240,7 @@ def streaming_bench(ds, dev, stream, n_chunks, n_layers=24):
                 s.step([tuple(x[l, a:a + Tc] for x in pools) for l in range(n_layers)],
                        k_rows[:, :Tc], v_rows[:, :Tc])
             else:
-                # the layers' inputs into the graph's input buffers (a model's
+                # the layers' inputs into the session's input buffers (a model's
                 # projections would write them there): timed apart from the step
                 for buf, x in zip(s.inputs, pools):
                     buf[:, :Tc].copy_(x[:, a:a + Tc])
