@@ -226,7 +226,7 @@ __device__ __forceinline__ float row_sq_sum16(half8 ef, int ln) {
 
 // Sequential kernel owning all d_v rows of a (stream, v-head) per workgroup
 // (gdn_wide.hip); returns the launch error.
-hipError_t launch_gdn_wide(const GdnArgs &a, int n_heads, int cus, bool o_bf16, bool drift,
+hipError_t launch_gdn_wide(const GdnArgs &a, int n_heads, int cus, bool prep_p, bool o_bf16, bool drift,
                            hipStream_t stream);
 
 }  // namespace ds

@@ -81,7 +81,7 @@ __device__ __forceinline__ void drift_setup(const GdnArgs &a, int tid, int nt) {
 // (lds_barrier, workgroup-wide), so that two groups of four waves of one
 // workgroup can each run a tile side by side.  write_q: this call writes the
 // tile's fp16 q fragments (when the workspace has them).  WP = false (the
-// whole-head sequential kernel, which forms P itself from the K and q tiles it
+// whole-head sequential kernel where it forms P itself from the K and q tiles it
 // stages): no q rows, no K Q^T and no P, and the first decay slot holds
 // gamma_r in base-2 units instead of Gamma_r.
 template <int D, bool WP = true>
@@ -1098,6 +1098,11 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // 8 heads 392 -> 363 us, 1024 tokens x 2 of 32 58 -> 57, 100 tokens x 2 of 32
 // 24 -> 22), at 72 ahead everywhere (4096 tokens 268 -> 194, 128 tokens 32 -> 24).
 constexpr int WIDE_MIN_HEADS = 64;
+// From WIDE_FORMS_P heads on the whole-head kernel forms P itself, from the fp16
+// copies of k and q that its other products read, except over layers at a pitch;
+// all other calls take P = scale D (.) tril(Q K^T) from the prep pass, whose Q K^T
+// runs on the bf16 inputs as they are (gdn_wide.hip has the figures of both).
+constexpr int WIDE_FORMS_P = 256;
 static bool use_wide(int B, int H_v, int d) { return d == 128 && (long long)B * H_v >= WIDE_MIN_HEADS; }
 
 // compute units of the current device (looked up once per device)
@@ -1161,6 +1166,7 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     a.wsP = p.wsP;
     // (a call without tokens takes the per-slice kernel, which only copies the state)
     const bool wide = D == 128 && use_wide(p.B, p.H_v, D) && p.tiles_max > 0;
+    const bool prep_p = !wide || p.pitch || (long long)p.B * p.H_v < WIDE_FORMS_P;
     a.wsQ = wide ? nullptr : p.wsQ;
     a.wsGam = p.wsGam;
     a.wsWrite = p.write_partials ? p.wsWrite : nullptr;
@@ -1194,18 +1200,17 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     if (p.tiles_max > 0 && !one_launch) {
         // tiles rounded up to a multiple of 8 (workgroups past the last tile exit)
         const long long n_prep = (long long)((p.tiles_max + 7) / 8) * 8 * (a.prep_per_vhead ? p.H_v : p.H_k);
-        // the whole-head kernel forms P itself (prep without q, K Q^T and P)
-        if (wide)
-            hipLaunchKernelGGL((gdn_prep_kernel<D, false>), dim3((unsigned)n_prep), dim3(256), 0, stream, a);
-        else
+        if (prep_p)
             hipLaunchKernelGGL((gdn_prep_kernel<D, true>), dim3((unsigned)n_prep), dim3(256), 0, stream, a);
+        else
+            hipLaunchKernelGGL((gdn_prep_kernel<D, false>), dim3((unsigned)n_prep), dim3(256), 0, stream, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     // the frame-end work is compiled out when neither drift sums nor snapshots are asked for
     const bool drift = p.drift_partials || p.snapshots;
     if (wide) {
-        hipError_t e = launch_gdn_wide(a, p.B * p.H_v, device_cus(), p.o_bf16, drift, stream);
+        hipError_t e = launch_gdn_wide(a, p.B * p.H_v, device_cus(), prep_p, p.o_bf16, drift, stream);
         if (e != hipSuccess) return e;
         if (p.write_partials && p.n_frames > 0) {
             hipLaunchKernelGGL(gdn_write_finalize_kernel, dim3(p.n_frames, p.H_v), dim3(256), 0, stream, p.wsWrite,

@@ -16,18 +16,27 @@
 //       from LDS (rows of K, Q, T, P, K^T) feeds both slices.
 //   waves 4-7 (loaders): load the tile two tiles ahead and stage it in LDS
 //       one tile ahead (K and q rows converted to fp16, the T fragments of the
-//       prep pass, v rows, gamma in base 2 and D_last); form P = scale D (.)
-//       tril(Q K^T) of the staged tile from its K and q on fp16 matrix cores,
-//       so that the prep pass reads no q and writes no P; and store the
-//       previous tile's bf16 o, which the compute waves left in LDS, as whole
-//       rows.  Loader 3 also adds the frame-end drift sums of the 8 slices
-//       (fixed order) and writes them, per slice or per head, with no exchange
-//       between workgroups.
-// Two barriers per tile (LDS-only): the tile's start, and one after the first
-// two products, before which the loaders stage the next tile's rows (P is
-// formed from them during the rest of the tile).  The state at a frame's
-// start, needed for ||S_end - S_start||^2, is kept in a scratch area of the
-// workspace (64 KiB per head) rather than in registers, and read back at the
+//       prep pass, v rows, gamma in base 2 and D_last); take P = scale D (.)
+//       tril(Q K^T) from the prep pass (PREP_P) or form it from the staged
+//       tile's K and q on fp16 matrix cores, so that the prep pass reads no q
+//       and writes no P; and store the previous tile's bf16 o, which the
+//       compute waves left in LDS, as whole rows.  Loader 3 also adds the
+//       frame-end drift sums of the 8 slices (fixed order) and writes them, per
+//       slice or per head, with no exchange between workgroups.
+// One barrier per tile (LDS-only), and where P is formed here a second one after
+// the first two products, before which the loaders stage the next tile's rows (P is
+// formed from them during the rest of the tile).
+//
+// P is formed here from 256 heads of packed streams on, where the prep pass is
+// bound by its traffic (the varlen batch 7.27 -> 7.04 ms).  That P comes from fp16
+// copies of k and q; calls of fewer heads, and layers at a pitch, keep the prep
+// pass's, formed from the bf16 inputs as they are, which is exact also where an
+// element of q lies below fp16's normal range.  (It costs a chunk of 125 tokens
+// through 24 layers of 32 heads 114.6 -> 116.8 us, and takes 4 ragged streams of
+// 32 heads on half heads, which would each form the head's P, 368 -> 348.)
+//
+// The state at a frame's start, needed for ||S_end - S_start||^2, is kept in a
+// scratch area of the workspace (64 KiB per head) rather than in registers, and read back at the
 // frame's end; for the first frame of a launch it is read from state_in again (an
 // empty buffer, which reads as zeros, without one), and nothing is kept once no
 // frame follows.  (The copies were a third of the traffic of a short call: one chunk
@@ -80,11 +89,11 @@ struct WideShared {
     float2 DR[2][4][2][64];   // frame-end drift sums per [frame % 2][compute wave][slice][lane]
 };
 
-// One loader's share of a tile: K, q and v rows 16 X .. 16 X + 15, T
-// fragments {2 X, 2 X + 1} (X < 2) or {4 + X - 2}; loader 0 also gamma (base
-// 2), loader 1 D_last.
+// One loader's share of a tile: K, q and v rows 16 X .. 16 X + 15, T (and, with
+// PREP_P, P) fragments {2 X, 2 X + 1} (X < 2) or {4 + X - 2}; loader 0 also gamma
+// (base 2; with PREP_P Gamma), loader 1 D_last.
 struct WideLoad {
-    u32x4 k[4], q[4], v[4], t[2];
+    u32x4 k[4], q[4], v[4], t[2], p[2];
     float g;
 };
 
@@ -112,11 +121,12 @@ __device__ int wide_cut(const GdnArgs &a) {
     return (top[S] + ft - 1) / ft * ft;
 }
 
+// PREP_P: P from the prep pass rather than formed by the loaders.
 // NSL = 2: one workgroup per (stream, v-head), compute wave w carrying rows
 // 32 w .. 32 w + 31; NSL = 1: two workgroups per (stream, v-head), each with
 // 64 rows (compute wave w: rows 64 h + 16 w .. + 15), for the tail of a split
 // call, where few streams are left and half heads put more CUs to work.
-template <bool OUT_BF16, bool DRIFT, int NSL>
+template <bool OUT_BF16, bool DRIFT, int NSL, bool PREP_P>
 __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
     constexpr int D = 128, KS = D / 32, NKB = D / 16;
     constexpr int HW = 2 / NSL;  // workgroups per head
@@ -356,7 +366,7 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
             }
             // second barrier: the loaders have staged the next tile and form its P
             // from it during (3) - (5) (P of the first tile is in LDS from here on)
-            lds_barrier();
+            if (!PREP_P) lds_barrier();
             // operands of (3) - (5): T diag(beta) and P fragments, D_last, the
             // scale Gamma of each token, the first K^T fragments
             half8 tf[6], pf[6], kt[2][2];
@@ -554,6 +564,11 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
                 const u32x4 *tb = (const u32x4 *)(a.wsT + tv * TP_HALVES);
 #pragma unroll
                 for (int c = 0; c < NT; ++c) s.t[c] = tb[(F_FIRST + c) * 64 + lane];
+                if (PREP_P) {
+                    const u32x4 *pb = (const u32x4 *)(a.wsP + tv * TP_HALVES);
+#pragma unroll
+                    for (int c = 0; c < NT; ++c) s.p[c] = pb[(F_FIRST + c) * 64 + lane];
+                }
                 if (X < 2) s.g = a.wsGam[tv * 128 + 64 * X + lane];
             };
             auto stage = [&](const WideLoad &s, auto bufc) __attribute__((always_inline)) {
@@ -570,10 +585,13 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
                     *(u32x4 *)(&sh.V[buf][row * WIDE_VLD + r0 + 8 * (lane % VCH)]) = s.v[c];
                 }
 #pragma unroll
-                for (int c = 0; c < NT; ++c) sh.T[buf][F_FIRST + c][lane] = s.t[c];
+                for (int c = 0; c < NT; ++c) {
+                    sh.T[buf][F_FIRST + c][lane] = s.t[c];
+                    if (PREP_P) sh.P[buf][F_FIRST + c][lane] = s.p[c];
+                }
                 if (X == 0) {
-                    sh.G[buf][0][lane] = __builtin_amdgcn_exp2f(s.g);
-                    sh.Gs[buf][lane] = s.g;
+                    sh.G[buf][0][lane] = PREP_P ? s.g : __builtin_amdgcn_exp2f(s.g);
+                    if (!PREP_P) sh.Gs[buf][lane] = s.g;
                 } else if (X == 1) {
                     sh.G[buf][1][lane] = s.g;
                 }
@@ -701,13 +719,13 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
                 // its global stores and loads follow it
                 auto step = [&](int it, WideLoad &s, auto bufc) __attribute__((always_inline)) {
                     lds_barrier();
-                    if (it == 0) form_p(std::integral_constant<int, 0>());
+                    if (!PREP_P && it == 0) form_p(std::integral_constant<int, 0>());
                     u32x4 ov[4];
                     if (OUT_BF16 && it >= 1) read_o(ov, bufc);
                     if (it + 1 < nt) stage(s, bufc);
-                    if (it < nt) lds_barrier();
+                    if (!PREP_P && it < nt) lds_barrier();
                     if (OUT_BF16 && it >= 1) store_o(lt0 + it - 1, ov);
-                    if (it + 1 < nt) form_p(bufc);
+                    if (!PREP_P && it + 1 < nt) form_p(bufc);
                     load(s, it + 3);
                     drift_reduce(it);
                 };
@@ -758,18 +776,18 @@ __global__ __launch_bounds__(512, 1) void gdn_wide_kernel(GdnArgs a) {
     }
 }
 
-template <int NSL>
+template <int NSL, bool PREP_P>
 static hipError_t launch_wide_nsl(const GdnArgs &a, int n_wg, bool o_bf16, bool drift, hipStream_t stream) {
     if (o_bf16) {
         if (drift)
-            hipLaunchKernelGGL((gdn_wide_kernel<true, true, NSL>), dim3(n_wg), dim3(512), 0, stream, a);
+            hipLaunchKernelGGL((gdn_wide_kernel<true, true, NSL, PREP_P>), dim3(n_wg), dim3(512), 0, stream, a);
         else
-            hipLaunchKernelGGL((gdn_wide_kernel<true, false, NSL>), dim3(n_wg), dim3(512), 0, stream, a);
+            hipLaunchKernelGGL((gdn_wide_kernel<true, false, NSL, PREP_P>), dim3(n_wg), dim3(512), 0, stream, a);
     } else {
         if (drift)
-            hipLaunchKernelGGL((gdn_wide_kernel<false, true, NSL>), dim3(n_wg), dim3(512), 0, stream, a);
+            hipLaunchKernelGGL((gdn_wide_kernel<false, true, NSL, PREP_P>), dim3(n_wg), dim3(512), 0, stream, a);
         else
-            hipLaunchKernelGGL((gdn_wide_kernel<false, false, NSL>), dim3(n_wg), dim3(512), 0, stream, a);
+            hipLaunchKernelGGL((gdn_wide_kernel<false, false, NSL, PREP_P>), dim3(n_wg), dim3(512), 0, stream, a);
     }
     return hipGetLastError();
 }
@@ -782,18 +800,25 @@ static hipError_t launch_wide_nsl(const GdnArgs &a, int n_wg, bool o_bf16, bool 
 // to the cut (the tile from which at most tail_streams streams are left,
 // on a frame boundary) and half heads from it, the second launch starting
 // from the states the first one wrote.
-hipError_t launch_gdn_wide(const GdnArgs &a0, int n_heads, int cus, bool o_bf16, bool drift, hipStream_t stream) {
+template <bool PREP_P>
+static hipError_t launch_wide(const GdnArgs &a0, int n_heads, int cus, bool o_bf16, bool drift, hipStream_t stream) {
     GdnArgs a = a0;
     a.wide_tail_streams = cus / (2 * a.H_v);
     a.wide_phase = 0;
-    if (2 * n_heads <= cus) return launch_wide_nsl<1>(a, 2 * n_heads, o_bf16, drift, stream);
+    if (2 * n_heads <= cus) return launch_wide_nsl<1, PREP_P>(a, 2 * n_heads, o_bf16, drift, stream);
     const bool split = a.wide_tail_streams >= 1 && a.frame_len > 0 && a.frame_len % TILE == 0;
     a.wide_phase = split ? 1 : 0;
-    hipError_t e = launch_wide_nsl<2>(a, n_heads, o_bf16, drift, stream);
+    hipError_t e = launch_wide_nsl<2, PREP_P>(a, n_heads, o_bf16, drift, stream);
     if (e != hipSuccess || !split) return e;
     a.wide_phase = 2;
     a.state_in = a.state_out;
-    return launch_wide_nsl<1>(a, 2 * n_heads, o_bf16, drift, stream);
+    return launch_wide_nsl<1, PREP_P>(a, 2 * n_heads, o_bf16, drift, stream);
+}
+
+hipError_t launch_gdn_wide(const GdnArgs &a, int n_heads, int cus, bool prep_p, bool o_bf16, bool drift,
+                           hipStream_t stream) {
+    return prep_p ? launch_wide<true>(a, n_heads, cus, o_bf16, drift, stream)
+                  : launch_wide<false>(a, n_heads, cus, o_bf16, drift, stream);
 }
 
 }  // namespace ds

@@ -2,9 +2,11 @@
 one gdn_chunk_fwd call per layer, and gdn_pack_layers against plain copies.
 
 Where both take the per-slice kernel the results are the same bits.  From 64
-heads on the layers take the whole-head kernel, whose operands are rounded to
-fp16 at the same places; o, the states and the drift sums then agree within
-2e-3, the bound both kernels keep against the oracle."""
+heads on the layers take the whole-head kernel: the same operations on the same
+operands, but where the compiler fuses a product with its rounding to fp16 in one
+kernel only, an element in about 2^13 may be rounded the other way (2^-11 of it):
+5e-6 of the norm, ten times that is allowed; a bf16 o may flip (2^-8) in one element
+in 2^10 besides."""
 import pytest
 import torch
 
@@ -62,9 +64,22 @@ def test_layers_match_one_call_per_layer(ds, L, T, pitch, H_k, H_v, d, odt, per_
     if L * H_v < 64 or d == 64:
         assert torch.equal(o[:, :T], ref_o) and torch.equal(S, ref_S) and torch.equal(p, ref_p)
     else:
-        assert rel(o[:, :T], ref_o) <= 2e-3 + (4e-3 if odt == torch.bfloat16 else 0)  # a bf16 output's own rounding
-        assert rel(S, ref_S) <= 2e-3 and rel(p, ref_p) <= 2e-3
+        assert rel(o[:, :T], ref_o) <= (5e-5 if odt == torch.float32 else 2e-4) and rel(S, ref_S) <= 5e-5
+        assert rel(p, ref_p) <= 1e-4
     assert bool((o[:, T:] == 5).all())
+
+
+def test_small_q_in_the_first_tile(ds):
+    """Layers on the whole-head kernel take P from the bf16 inputs: a q whose fp16 copies would be subnormal costs the
+    first tile's o nothing."""
+    L, T, H_k, H_v, d, scale = 24, 64, 8, 16, 128, 2.0 ** 17
+    xs = [((x[0].float() / scale).to(torch.bfloat16),) + x[1:] for x in layers(L, T, H_k, H_v, d)]
+    S, p = torch.zeros(L, 1, H_v, d, d, device=DEV), torch.empty(L, 1, H_v, 2, device=DEV)
+    o = torch.empty(L, T, H_v, d, device=DEV)
+    ws = torch.empty(ds.gdn_workspace_bytes(ds.gdn_shape([T] * L, H_k, H_v, d, 0)), dtype=torch.uint8, device=DEV)
+    ds.gdn_layers_fwd(*packed_like(ds, xs, T, T), T, S, o, p, ws, scale=scale)
+    for l, x in enumerate(xs):
+        assert rel(o[l], ds.gdn_chunk_fwd(*x, [T], 0, scale=scale)["o"]) <= 5e-5, l
 
 
 @pytest.mark.parametrize("L,T,pitch,H_k,H_v,d", [(1, 1, 1, 1, 1, 64), (64, 3, 5, 1, 2, 64), (65, 2, 2, 1, 3, 64),

@@ -233,3 +233,35 @@ def test_no_tokens(ds, B):
                                 None, None, P(ws), ws.numel(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     torch.cuda.synchronize()
     assert rc == 0 and torch.equal(S0, S1) and torch.all(dp == 0.0)
+
+
+@pytest.mark.parametrize("T,H_k,H_v,frame_len,odt", [(64, 36, 72, 0, torch.float32), (333, 12, 72, 128, torch.float32),
+                                                     (700, 36, 144, 64, torch.bfloat16), (129, 66, 132, 0, torch.float32)])
+def test_heads_of_larger_calls(ds, T, H_k, H_v, frame_len, odt):
+    """Calls of fewer than 256 heads take P from the prep pass (Q K^T on the bf16
+    inputs) on either sequential kernel: the heads of one call have the o and the
+    states that they have in calls of fewer heads (per-slice kernel), also where fp16
+    copies of q would be subnormal, and in the first tile such a q costs o nothing
+    against the oracle.  The same operations in both, but the compiler fuses a few of
+    the products with their rounding to fp16 in one and not in the other: an element in
+    about 2^13 is then rounded twice and may flip (2^-11 of it), 5e-6 of the norm; ten
+    times that, and for a bf16 o a flip (2^-8) of one element in 2^10 besides."""
+    x = synth.make_gdn_inputs([T], H_k, H_v, 128, frame_len, novelty=True, config=5, layer=21)
+    small = torch.tensor(2.0 ** -17)
+    q = (dev_bf16(x.q).float() * small.to(DEV)).to(torch.bfloat16)   # exact: a power of two
+    scale = float(2.0 ** 17)
+    k, v, g, beta = dev_bf16(x.k), dev_bf16(x.v), dev_f32(x.g), dev_f32(x.beta)
+    for qq, sc in ((dev_bf16(x.q), 1.0), (q, scale)):
+        big = ds.gdn_chunk_fwd(qq, k, v, g, beta, [T], frame_len, o_dtype=odt, scale=sc)
+        n, r = H_k // 6, H_v // H_k   # six calls of a sixth of the heads each
+        for i in range(6):
+            hk, hv = slice(i * n, (i + 1) * n), slice(i * n * r, (i + 1) * n * r)
+            c = lambda t, h: t[:, h].contiguous()  # noqa: E731
+            part = ds.gdn_chunk_fwd(c(qq, hk), c(k, hk), c(v, hv), c(g, hv), c(beta, hv), [T], frame_len, o_dtype=odt, scale=sc)
+            rel = lambda a, b: float((a.double() - b.double()).norm() / b.double().norm())  # noqa: E731
+            eo, es = rel(big["o"][:, hv], part["o"]), rel(big["state"][:, hv], part["state"])
+            assert eo <= (5e-5 if odt == torch.float32 else 2e-4) and es <= 5e-5, (i, sc, eo, es)
+            assert rel(big["drift_partials"][:, hv], part["drift_partials"]) <= 1e-4, (i, sc)
+    ref = oracle.gdn_forward(x.q, x.k, x.v, x.g, x.beta, x.cu_seqlens, frame_len)
+    n = min(T, 64)   # behind the first tile the state meets an fp16 q, which such values do round
+    assert rel_fro(big["o"][:n].float().cpu().numpy(), ref["o"][:n]) <= TOL_O * (1 if odt == torch.float32 else 2)
