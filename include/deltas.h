@@ -163,6 +163,18 @@ ds_status gdn_chunk_fwd(const ds_gdn_shape *shape, const void *q, const void *k,
                         float scale, float *drift_partials, float *write_partials, float *snapshots,
                         void *workspace, size_t workspace_bytes, void *stream);
 
+/* gdn_chunk_fwd for a caller that knows the longest stream: `longest` is the
+ * number of tokens of the longest of the B streams (0: not known, which is
+ * gdn_chunk_fwd).  It only chooses between kernels -- batches of 64 to 255
+ * (stream, v-head) pairs run on the one that is faster for streams of about
+ * equal lengths, or on the other -- and need not be exact (a graph may be
+ * replayed with other lengths). */
+ds_status gdn_chunk_fwd_longest(const ds_gdn_shape *shape, int32_t longest, const void *q, const void *k,
+                                const void *v, const float *g, const float *beta, const int32_t *cu_seqlens,
+                                const float *state_in, float *state_out, void *o, int32_t o_dtype, float scale,
+                                float *drift_partials, float *write_partials, float *snapshots, void *workspace,
+                                size_t workspace_bytes, void *stream);
+
 /* ------------------------------------------------------------------------
  * gdn_layers_fwd -- gdn_chunk_fwd over independent layers of equal length
  * ------------------------------------------------------------------------

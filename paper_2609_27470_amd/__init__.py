@@ -24,7 +24,7 @@ EXPORTED = [
     "gdn_chunk_fwd", "deltas_drift",
     "deltas_drift_states", "ds_kv_workspace_bytes", "kv_evict_topk", "ds_kv_device_status",
     "ds_kv_indexed_workspace_bytes", "kv_evict_topk_indexed", "gdn_decode_step", "kv_evict_topk_indexed_noalloc",
-    "kv_append_indexed", "gdn_layers_fwd", "gdn_pack_layers",
+    "kv_append_indexed", "gdn_layers_fwd", "gdn_pack_layers", "gdn_chunk_fwd_longest",
 ]
 NOALLOC_MAX_CAPACITY = 65536
 
@@ -66,6 +66,8 @@ def lib():
         L.gdn_chunk_fwd.argtypes = [ctypes.POINTER(GdnShape), P, P, P, P, P, P, P, P, P, I32, ctypes.c_float,
                                     P, P, P, P, SZ, P]
         L.gdn_chunk_fwd.restype = I32
+        L.gdn_chunk_fwd_longest.argtypes = [ctypes.POINTER(GdnShape), I32] + L.gdn_chunk_fwd.argtypes[1:]
+        L.gdn_chunk_fwd_longest.restype = I32
         L.gdn_decode_step.argtypes = [I32, I32, I32, I32, I32, P, P, P, P, P, P, P, P, I32, ctypes.c_float, P]
         L.gdn_decode_step.restype = I32
         L.deltas_drift.argtypes = [P, I32, I32, I32, I32, P, P]
@@ -150,12 +152,13 @@ def gdn_chunk_fwd(q, k, v, g, beta, lengths, frame_len, cu_seqlens=None, state_i
     """
     T, H_k, d = q.shape
     H_v = v.shape[1]
+    lengths = [int(n) for n in lengths]
     shape = gdn_shape(lengths, H_k, H_v, d, frame_len, drift_per_slice)
     dev = q.device
     if cu_seqlens is None and shape.B > 1:
         cu = [0]
         for n in lengths:
-            cu.append(cu[-1] + int(n))
+            cu.append(cu[-1] + n)
         cu_seqlens = torch.tensor(cu, dtype=torch.int32, device=dev)
     if state_out is None:
         state_out = torch.empty((shape.B, H_v, d, d), dtype=torch.float32, device=dev)
@@ -172,9 +175,10 @@ def gdn_chunk_fwd(q, k, v, g, beta, lengths, frame_len, cu_seqlens=None, state_i
     need = gdn_workspace_bytes(shape, wp is not None)
     if workspace is None or workspace.numel() < need:
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
-    _check(lib().gdn_chunk_fwd(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
-                               _ptr(cu_seqlens), _ptr(state_in), _ptr(state_out), _ptr(o), od, float(scale),
-                               _ptr(dp), _ptr(wp), _ptr(sn), _ptr(workspace), workspace.numel(), _stream(stream)))
+    _check(lib().gdn_chunk_fwd_longest(ctypes.byref(shape), max(lengths, default=0), _ptr(q), _ptr(k), _ptr(v), _ptr(g),
+                                       _ptr(beta), _ptr(cu_seqlens), _ptr(state_in), _ptr(state_out), _ptr(o), od, float(scale),
+                                       _ptr(dp), _ptr(wp), _ptr(sn), _ptr(workspace), workspace.numel(),
+                                       _stream(stream)))
     return dict(o=o, state=state_out, drift_partials=dp, write_partials=wp, snapshots=sn, workspace=workspace)
 
 

@@ -78,8 +78,8 @@ size_t ds_gdn_write_workspace_bytes(const ds_gdn_shape *shape) {
         .total;
 }
 
-// gdn_chunk_fwd (pitch 0) and gdn_layers_fwd
-static ds_status gdn_forward(const ds_gdn_shape *shape, int32_t pitch, const void *q, const void *k, const void *v,
+// gdn_chunk_fwd, gdn_chunk_fwd_longest (pitch 0) and gdn_layers_fwd (longest 0)
+static ds_status gdn_forward(const ds_gdn_shape *shape, int32_t longest, int32_t pitch, const void *q, const void *k, const void *v,
                              const float *g, const float *beta, const int32_t *cu_seqlens, const float *state_in,
                              float *state_out, void *o, int32_t o_dtype, float scale, float *drift_partials,
                              float *write_partials, float *snapshots, void *workspace, size_t workspace_bytes,
@@ -114,6 +114,7 @@ static ds_status gdn_forward(const ds_gdn_shape *shape, int32_t pitch, const voi
     p.cu_seqlens = cu_seqlens;
     p.B = s.B;
     p.T_total = s.T_total;
+    p.longest = longest;
     p.pitch = pitch;
     p.H_k = s.H_k;
     p.H_v = s.H_v;
@@ -151,8 +152,19 @@ ds_status gdn_chunk_fwd(const ds_gdn_shape *shape, const void *q, const void *k,
                         float *snapshots,
                         void *workspace, size_t workspace_bytes, void *stream) {
     g_last_error[0] = 0;
-    return gdn_forward(shape, 0, q, k, v, g, beta, cu_seqlens, state_in, state_out, o, o_dtype, scale, drift_partials,
-                       write_partials, snapshots, workspace, workspace_bytes, stream);
+    return gdn_forward(shape, 0, 0, q, k, v, g, beta, cu_seqlens, state_in, state_out, o, o_dtype, scale,
+                       drift_partials, write_partials, snapshots, workspace, workspace_bytes, stream);
+}
+
+ds_status gdn_chunk_fwd_longest(const ds_gdn_shape *shape, int32_t longest, const void *q, const void *k,
+                                const void *v, const float *g, const float *beta, const int32_t *cu_seqlens,
+                                const float *state_in, float *state_out, void *o, int32_t o_dtype, float scale,
+                                float *drift_partials, float *write_partials, float *snapshots, void *workspace,
+                                size_t workspace_bytes, void *stream) {
+    g_last_error[0] = 0;
+    if (longest < 0) return fail(DS_E_ARG, "longest=%d", longest);
+    return gdn_forward(shape, longest, 0, q, k, v, g, beta, cu_seqlens, state_in, state_out, o, o_dtype, scale,
+                       drift_partials, write_partials, snapshots, workspace, workspace_bytes, stream);
 }
 
 ds_status gdn_layers_fwd(const ds_gdn_shape *shape, int32_t pitch, const void *q, const void *k, const void *v,
@@ -167,7 +179,7 @@ ds_status gdn_layers_fwd(const ds_gdn_shape *shape, int32_t pitch, const void *q
         return fail(DS_E_SHAPE, "pitch=%d is less than the %d tokens of a layer", pitch, shape->T_total / shape->B);
     if (shape->H_v >= 1 && (long long)pitch * shape->B > (1LL << 30) / shape->H_v)
         return fail(DS_E_UNSUPPORTED, "problem too large for one call");
-    return gdn_forward(shape, pitch, q, k, v, g, beta, nullptr, state_in, state_out, o, o_dtype, scale, drift_partials,
+    return gdn_forward(shape, 0, pitch, q, k, v, g, beta, nullptr, state_in, state_out, o, o_dtype, scale, drift_partials,
                        nullptr, nullptr, workspace, workspace_bytes, stream);
 }
 

@@ -1088,22 +1088,36 @@ __global__ __launch_bounds__(256) void gdn_write_finalize_kernel(const float *ws
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The sequential part runs one or two workgroups per (stream, v-head)
-// (gdn_wide.hip) from WIDE_MIN_HEADS heads on; below, one workgroup per 16-row
-// slice of a head (8 per head at d = 128).  The slices fill the GPU from 32
-// heads, but each of them loads the whole tile, so from there on their time
-// grows with the heads (8192 tokens per stream of 32 heads: 186, 352, 480, 627,
-// 1092 us a call with 1, 2, 3, 4, 7 streams); half or whole heads load it two
-// times or once, and their time grows only once the CUs are full (310, 335, 378,
-// 415, 578 us).  At 64 heads they are level or ahead (8191 tokens x 8 streams of
-// 8 heads 392 -> 363 us, 1024 tokens x 2 of 32 58 -> 57, 100 tokens x 2 of 32
-// 24 -> 22), at 72 ahead everywhere (4096 tokens 268 -> 194, 128 tokens 32 -> 24).
+// (gdn_wide.hip) or one workgroup per 16-row slice of a head (8 per head at d =
+// 128).  The slices fill the GPU from 32 heads, but each of them loads the whole
+// tile, so from there on a tile's time grows with the heads that are live; half or
+// whole heads load it twice or once, and its time grows slowly (8192 tokens per
+// stream of 32 heads, 2, 3, 4, 7 streams: 315, 469, 621, 1081 us a call on slices;
+// 304, 347, 391, 598 on half or whole heads).  One stream of 64 heads takes 25.3 us
+// on slices and 19.4 on half heads at 128 tokens, 150 and 145 at 4096; of 72 heads
+// 41.6 and 20.9, 301 and 159.
+// Where the streams differ in length, what counts is the number of heads that are
+// live on average over the longest one: a tile with h of them takes about 0.25 +
+// 0.037 h us on slices, 1.7 + 0.01 h on half and 2.4 + 0.01 h on whole heads.  Slices
+// and half heads, us: mean 34 (16384 and 1024 tokens x 32 heads) 333 and 530, 48
+// (16384, 8192) 464 and 572, 54 (3 streams of up to 13321) 437 and 480, 60 (8192, 4096,
+// 2048, 1024) 305 and 300, 66 355 and 335, 82 613 and 499; slices and whole heads: 63
+// 915 and 936, 66 433 and 434 (459 without frames), 70 523 and 492 (538), 76 149 and
+// 136, 81 786 and 676 (731).  Without the longest stream's length the slices.
+// Calls of at most WIDE_SMALL tokens are level or faster on half or whole heads
+// whatever the lengths (254 and 2 tokens x 32 heads 23.4 and 22.0, twice 1 token
+// 22.6 and 15.8).
 constexpr int WIDE_MIN_HEADS = 64;
+constexpr int WIDE_LIVE_HALF = 62, WIDE_LIVE_WHOLE = 72;
+constexpr int WIDE_SMALL = 256;
+// calls whose workspace has what the whole-head kernel needs
+static bool use_wide(int B, int H_v, int d) { return d == 128 && (long long)B * H_v >= WIDE_MIN_HEADS; }
+
 // From WIDE_FORMS_P heads on the whole-head kernel forms P itself, from the fp16
 // copies of k and q that its other products read, except over layers at a pitch;
 // all other calls take P = scale D (.) tril(Q K^T) from the prep pass, whose Q K^T
 // runs on the bf16 inputs as they are (gdn_wide.hip has the figures of both).
 constexpr int WIDE_FORMS_P = 256;
-static bool use_wide(int B, int H_v, int d) { return d == 128 && (long long)B * H_v >= WIDE_MIN_HEADS; }
 
 // compute units of the current device (looked up once per device)
 static int device_cus() {
@@ -1118,6 +1132,15 @@ static int device_cus() {
     return cus[dev];
 }
 
+// The whole-head kernel for this call (with tokens), or the per-slice one.
+static bool takes_wide(const GdnLaunch &p) {
+    if (!use_wide(p.B, p.H_v, p.d) || p.tiles_max == 0) return false;
+    const int heads = p.B * p.H_v;
+    if (p.B == 1 || p.pitch || heads >= WIDE_FORMS_P || p.T_total <= WIDE_SMALL) return true;
+    const int live = 2 * heads <= device_cus() ? WIDE_LIVE_HALF : WIDE_LIVE_WHOLE;
+    return p.longest > 0 && (long long)p.T_total * p.H_v >= (long long)p.longest * live;
+}
+
 GdnWorkspace gdn_workspace_layout(int B, int T_total, int H_k, int H_v, int d, int n_frames, bool with_write) {
     GdnWorkspace w{};
     w.tiles_max = (int)(((long long)T_total + 63LL * B) / 64);
@@ -1128,7 +1151,7 @@ GdnWorkspace gdn_workspace_layout(int B, int T_total, int H_k, int H_v, int d, i
     w.offP = off;
     off = align256(off + (size_t)w.tiles_max * H_v * TP_HALVES * sizeof(_Float16));
     w.offQ = off;  // fp16 q fragments, only for the per-slice kernel
-    if (!use_wide(B, H_v, d)) off = align256(off + (size_t)w.tiles_max * H_k * 64 * d * sizeof(_Float16));
+    if (!use_wide(B, H_v, d) || (long long)B * H_v < WIDE_FORMS_P) off = align256(off + (size_t)w.tiles_max * H_k * 64 * d * sizeof(_Float16));
     w.offGam = off;
     off = align256(off + (size_t)w.tiles_max * H_v * 128 * sizeof(float));
     w.offDrift = off;
@@ -1165,7 +1188,7 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     a.wsT = p.wsT;
     a.wsP = p.wsP;
     // (a call without tokens takes the per-slice kernel, which only copies the state)
-    const bool wide = D == 128 && use_wide(p.B, p.H_v, D) && p.tiles_max > 0;
+    const bool wide = D == 128 && takes_wide(p);
     const bool prep_p = !wide || p.pitch || (long long)p.B * p.H_v < WIDE_FORMS_P;
     a.wsQ = wide ? nullptr : p.wsQ;
     a.wsGam = p.wsGam;

@@ -12,6 +12,7 @@ struct GdnLaunch {
     const float *g, *beta;
     const int32_t *cu_seqlens;
     int B, T_total, H_k, H_v, d;  // d = d_k = d_v
+    int longest;                  // tokens of the longest of B > 1 packed streams, 0: the host does not know
     int pitch;                    // 0: packed streams; else stream b's T_total / B tokens start at token b * pitch
     int frame_len, n_frames;
     const float *state_in;

@@ -101,6 +101,20 @@ def test_gdn_rejects_bad_arguments(ds):
     assert b"cu_seqlens" in ds.lib().ds_last_error()
 
 
+def test_longest_stream_rejects_bad_arguments(ds):
+    """gdn_chunk_fwd_longest refuses what gdn_chunk_fwd refuses, and a negative length."""
+    L, P = ds.lib(), ctypes.c_void_p
+    fake = P(1 << 20)
+    call = lambda shape, longest, q=fake, ws=1 << 40: L.gdn_chunk_fwd_longest(  # noqa: E731
+        ctypes.byref(shape), longest, q, fake, fake, fake, fake, fake, None, fake, fake, ds.DS_F32, 1.0, None, None, None,
+        fake, ws, None)
+    good = ds.gdn_shape([100, 200], 2, 4, 64, 256)
+    assert call(good, -1) == 6
+    assert b"longest" in L.ds_last_error()
+    assert call(good, 200, q=None) == 1 and call(good, 0, ws=16) == 8
+    assert call(ds.gdn_shape([64], 3, 4, 64, 64), 64) == 2
+
+
 def test_drift_rejects_bad_arguments(ds):
     L = ds.lib()
     assert L.deltas_drift(None, 1, 1, 1, 9, None, None) == 6
