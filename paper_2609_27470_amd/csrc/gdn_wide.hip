@@ -97,28 +97,56 @@ struct WideLoad {
     float g;
 };
 
-// The tile index from which at most a.wide_tail_streams streams have tiles
-// left, rounded up to a frame boundary (every workgroup computes the same
-// value from the device lengths): the cut between the whole-head launch
-// and the half-head launch of a split call.
-__device__ int wide_cut(const GdnArgs &a) {
-    constexpr int MAXS = 16;
-    int top[MAXS + 1];  // the largest tile counts, descending
-    const int S = min(a.wide_tail_streams, MAXS);
-    for (int i = 0; i <= S; ++i) top[i] = 0;
-    for_streams(a.st, [&](int, int s0, int e0) {
-        int v = (e0 - s0 + TILE - 1) / TILE;
-        for (int i = 0; i <= S; ++i) {  // insert, keeping the S + 1 largest
-            if (v > top[i]) {
-                const int t = top[i];
-                top[i] = v;
-                v = t;
-            }
+// Calls f(n) with the tiles n of stream i + lane in each lane (0 past the last
+// stream), for i = 0, 64, ..., by a whole wave: the streams of for_streams, whose
+// sanitised ends are a running maximum of cu_seqlens.
+template <typename F>
+__device__ __forceinline__ void for_lane_tiles(const Streams &s, F f) {
+    const int lane = threadIdx.x & 63;
+    if (s.T < 0 || !s.cu) {  // at a pitch, or one stream
+        const int n = ((s.T < 0 ? -s.T : s.T) + TILE - 1) / TILE;
+        for (int i = 0; i < s.B; i += 64) f(i + lane < s.B ? n : 0);
+        return;
+    }
+    int end = min(max(s.cu[0], 0), s.T);  // of the streams before
+    for (int i = 0; i < s.B; i += 64) {
+        int e = i + lane < s.B ? min(s.cu[i + lane + 1], s.T) : 0;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(e, d, 64);
+            if (lane >= d) e = max(e, up);
         }
-        return false;
-    });
+        e = max(e, end);
+        const int before = __shfl_up(e, 1, 64);
+        f((e - (lane > 0 ? before : end) + TILE - 1) / TILE);
+        end = __shfl(e, 63, 64);
+    }
+}
+
+// The tile index from which at most a.wide_tail_streams streams have tiles
+// left, rounded up to a frame boundary (every wave computes the same value from
+// the device lengths): the cut between the whole-head launch and the half-head
+// launch of a split call.  A binary search over the tiles with 64 streams per
+// count.  (Inserting stream after stream into a list of the longest took 100 us a
+// launch at 64 streams: 64 streams of 64 tokens x 3 heads 236 -> 68 us a call, x 4
+// 239 -> 70, 256 streams x 1 884 -> 204.)
+__device__ int wide_cut(const GdnArgs &a) {
+    int lo = 0, hi = 0;
+    for_lane_tiles(a.st, [&](int n) { hi = max(hi, n); });
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) hi = max(hi, __shfl_xor(hi, d, 64));
+    hi = __builtin_amdgcn_readfirstlane(hi);
+    while (lo < hi) {  // the least m with at most wide_tail_streams streams of more than m tiles
+        const int m = (lo + hi) >> 1;
+        int more = 0;
+        for_lane_tiles(a.st, [&](int n) { more += __popcll(__ballot(n > m)); });
+        if (more <= a.wide_tail_streams)
+            hi = m;
+        else
+            lo = m + 1;
+    }
     const int ft = a.frame_len / TILE;
-    return (top[S] + ft - 1) / ft * ft;
+    return (lo + ft - 1) / ft * ft;
 }
 
 // PREP_P: P from the prep pass rather than formed by the loaders.

@@ -335,3 +335,19 @@ def test_one_long_stream_among_short_ones_takes_its_own_time(ds, short, frame_le
                                                  drift_partials=r["drift_partials"], workspace=r["workspace"]))
     alone, together = call([16384]), call([16384] + short)
     assert together <= 1.35 * alone, (together, alone)
+
+
+def test_cut_of_many_streams_is_found_quickly(ds):
+    """64 streams x 3 heads: the call split at a frame boundary (two launches) takes
+    little longer than the same call as one launch; inserting the streams one after
+    the other into a list of the longest cost 100 us a launch."""
+    B, H, d = 64, 3, 128
+    x = synth.make_gdn_inputs([64] * B, H, H, d, 64, novelty=True, config=5, layer=33)
+    args = [dev_bf16(x.q), dev_bf16(x.k), dev_bf16(x.v), dev_f32(x.g), dev_f32(x.beta), lengths_of(x)]
+    cu = torch.from_numpy(np.asarray(x.cu_seqlens, np.int32)).to(DEV)
+    t = {}
+    for frame_len in (0, 64):
+        r = ds.gdn_chunk_fwd(*args, frame_len, cu_seqlens=cu)
+        t[frame_len] = _fastest(lambda: ds.gdn_chunk_fwd(*args, frame_len, cu_seqlens=cu, state_out=r["state"], o=r["o"],
+                                                         drift_partials=r["drift_partials"], workspace=r["workspace"]), 20)
+    assert t[64] <= 2.0 * t[0] + 0.02, t

@@ -1,5 +1,6 @@
-"""CPU models of two steps of the prep pass, written in the order the kernel
-takes them, checked against plain definitions (CPU only).
+"""CPU models of two steps of the prep pass, and of how the whole-head kernel finds
+its streams' tiles and the cut of a split call, written in the order the kernels
+take them, checked against plain definitions (CPU only).
 
 - The inverse T = (I + A)^-1 of the strictly lower-triangular A of a 64-token
   tile (the UT transform of the chunkwise form, A_ri = beta_r D_ri k_r . k_i
@@ -134,3 +135,67 @@ def test_wave_prefix_sum_is_the_inclusive_scan():
     x = np.zeros(64)
     x[[0, 15, 16, 31, 47, 63]] = 1.0
     assert np.array_equal(wave_prefix_sum(x), np.cumsum(x))
+
+
+def _serial_streams(cu, T):
+    """The sanitised (start, end) of every stream, walked in order."""
+    out, prev = [], 0
+    for b in range(len(cu) - 1):
+        st = min(max(cu[b], prev), T)
+        en = min(max(cu[b + 1], st), T)
+        out.append((st, en))
+        prev = en
+    return out
+
+
+def _lane_tiles(cu, T):
+    """The whole-head kernel's lane-parallel form: ends as a running maximum, 64 streams at a time."""
+    B, tiles = len(cu) - 1, []
+    end = min(max(cu[0], 0), T)
+    for i in range(0, B, 64):
+        e = [min(cu[i + l + 1], T) if i + l < B else 0 for l in range(64)]
+        d = 1
+        while d < 64:
+            e = [max(e[l], e[l - d]) if l >= d else e[l] for l in range(64)]
+            d *= 2
+        e = [max(x, end) for x in e]
+        n = [(e[l] - (e[l - 1] if l else end) + 63) // 64 for l in range(64)]
+        assert all(x == 0 for x in n[max(0, B - i):])
+        tiles += n[:min(64, B - i)]
+        end = e[63]
+    return tiles
+
+
+def _cut(tiles, S, ft):
+    lo, hi = 0, max(tiles, default=0)
+    while lo < hi:
+        m = (lo + hi) // 2
+        if sum(n > m for n in tiles) <= S:
+            hi = m
+        else:
+            lo = m + 1
+    return -(-lo // ft) * ft
+
+
+@pytest.mark.parametrize("B", [1, 2, 5, 63, 64, 65, 130, 300])
+def test_lane_parallel_stream_tiles_and_cut(B):
+    """Tiles per stream and the cut of a split call against the serial walk and a sort, for any cu_seqlens (descending,
+    negative, past the end included)."""
+    rng = np.random.default_rng(B)
+    for trial in range(40):
+        lens = rng.integers(0, 400, B)
+        cu = np.concatenate([[0], np.cumsum(lens)])
+        T = int(cu[-1])
+        if trial % 4 == 1:
+            cu = cu + rng.integers(-200, 200, B + 1)
+        elif trial % 4 == 2:
+            cu = rng.integers(-500, 2 * T + 2, B + 1)
+        elif trial % 4 == 3:
+            T //= 2
+        cu = [int(c) for c in cu]
+        want = [-(-(e - s) // 64) for s, e in _serial_streams(cu, T)]
+        assert _lane_tiles(cu, T) == want
+        for S in (0, 1, 4, 16, 42, 400):
+            for ft in (1, 4):
+                top = sorted(want, reverse=True) + [0] * (S + 1)
+                assert _cut(want, S, ft) == -(-top[S] // ft) * ft
