@@ -228,6 +228,7 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         s_bad = 0;
     }
     if (tid < a.n_planes) a.plane_tab[tid] = a.planes[tid];
+    lds_sync();  // s_bad is cleared before any wave can raise it
 
     const int c0 = a.n_s, c1 = a.len - a.n_w;
 

@@ -433,3 +433,26 @@ def test_selection_edges(ds, n, runs, M, ns, nw, nb):
     scores = rng.choice([0.1, 0.2, 0.5, 1.0, np.inf], size=runs).astype(np.float32)
     one_event(ds, 1, 8, chunk, pos, scores, M, ns, nw, nb)
     indexed_event(ds, chunk, pos, scores, M, ns, nw, nb, seed=2)
+
+
+@pytest.mark.parametrize("n,at", [(700, 1), (700, 699), (5000, 4096), (20480, 257), (20480, 20479), (41000, 1024),
+                                  (41000, 15 * 256 + 3), (41000, 20480), (41000, 25000), (41000, 40999)])
+def test_one_violation_anywhere_leaves_the_cache_untouched(ds, n, at):
+    """A position that repeats its predecessor, seen by one lane of one wave (the first wave, which clears the flag it
+    raises, the last, a later block or step): nothing is moved or rewritten, in either form of the cache."""
+    chunk = torch.arange(n, dtype=torch.int32, device=DEV) // 50
+    pos = torch.arange(n, dtype=torch.int32, device=DEV)
+    pos[at] = pos[at - 1]
+    scores = torch.rand(int(chunk[-1]) + 1, device=DEV)
+    M = n - 40
+    k = torch.randint(-99, 99, (n, 8), dtype=torch.int16, device=DEV)
+    k0, p0, c0, keep = k.clone(), pos.clone(), chunk.clone(), torch.full((M,), -1, dtype=torch.int32, device=DEV)
+    _, ws = ds.kv_evict_topk([k], [k0.clone()], pos, chunk, scores, n, M, 4, 100, 2, keep_out=keep)
+    assert ds.kv_device_status(ws)[0] == 1
+    assert torch.equal(k, k0) and torch.equal(pos, p0) and torch.equal(chunk, c0) and bool((keep == -1).all())
+    slot = torch.randperm(n, device=DEV).to(torch.int32)
+    s0, free = slot.clone(), torch.full((40,), -1, dtype=torch.int32, device=DEV)
+    _, ws, _ = ds.kv_evict_topk_indexed(pos, chunk, slot, scores, n, M, 4, 100, 2, keep_out=keep, free_out=free)
+    assert ds.kv_device_status(ws)[0] == 1
+    assert torch.equal(pos, p0) and torch.equal(chunk, c0) and torch.equal(slot, s0)
+    assert bool((keep == -1).all()) and bool((free == -1).all())
