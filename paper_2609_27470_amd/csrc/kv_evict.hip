@@ -499,7 +499,11 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
 
     // ---- keep list (ascending) and, indexed, the freed slots: the sinks, of
     // every run the slots from run_from on (those before it are evicted), the
-    // window.  A wave writes a run, or several waves one where the runs are few.
+    // window.  A wave writes a run, several waves one where the runs are few, and as
+    // many lanes as an average run is long where they are short: a turn of a wave
+    // takes 0.35 us however little it writes (8317 slots in 1040 runs 81 -> 62 us with
+    // 8 lanes a run, 2080 of 4 tokens 132 -> 90); runs much longer than that are
+    // left to whole waves.
     int total_kept = c0;
     int first_move = a.M;  // smallest destination d with keep[d] != d
     const int n_evict = a.len - a.M;
@@ -510,6 +514,9 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         if (d < SEL_STEP) s_keep[d] = i;
     };
     for (int i = tid; i < c0; i += SEL_THREADS) put(i, i);
+    int gl = 64;  // lanes per run
+    while (gl > 4 && (long long)(gl / 2) * R >= ncand) gl >>= 1;
+    __shared__ int s_long;  // the batch's long runs, listed in the second half of s_ord
     for (int rb = 0; rb < R; rb += SEL_THREADS) {
         const int r = rb + tid, n = min(R - rb, SEL_THREADS);
         const int from = r < R ? run_from(r) : 0, kept = r < R ? run_start(r + 1) - from : 0;
@@ -517,16 +524,28 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         const int dst = total_kept + block_excl_scan(kept, s_scan, tot);
         if (kept > 0 && from != dst) first_move = min(first_move, dst);
         s_ord[tid] = dst;
+        if (tid == 0) s_long = 0;
         lds_sync();
         constexpr int W = SEL_THREADS / 64;
-        const int per = max(1, W / n), lane = tid & 63, i0 = wid % per * 64 + lane, step = 64 * per;
-        for (int q = wid / per; q < n; q += W / per) {
+        const int lane = tid & 63;
+        auto put_run = [&](int q, int i0, int step) __attribute__((always_inline)) {
             const int to = s_ord[q], st = run_start(rb + q), fr = run_from(rb + q), en = run_start(rb + q + 1);
             for (int i = fr + i0; i < en; i += step) put(to + i - fr, i);
             if (a.slot) {  // st - to tokens were evicted before this run
                 for (int i = st + i0; i < fr; i += step)
                     if (i - to < n_evict) a.free_out[i - to] = a.slot[i];
             }
+        };
+        if (gl == 64) {
+            const int per = max(1, W / n);
+            for (int q = wid / per; q < n; q += W / per) put_run(q, wid % per * 64 + lane, 64 * per);
+        } else {
+            auto is_long = [&](int q) { return run_start(rb + q + 1) - run_start(rb + q) > 8 * gl; };
+            if (r < R && is_long(tid)) s_ord[SEL_THREADS + atomicAdd(&s_long, 1)] = tid;
+            for (int q = tid / gl; q < n; q += SEL_THREADS / gl)
+                if (!is_long(q)) put_run(q, tid % gl, gl);
+            lds_sync();
+            for (int l = wid; l < s_long; l += W) put_run(s_ord[SEL_THREADS + l], lane, 64);
         }
         lds_sync();
         total_kept += tot;

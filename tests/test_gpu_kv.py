@@ -422,10 +422,12 @@ def test_many_strips_of_wide_rows(ds):
     (20480, 1, 20479, 0, 0, 1), (20481, 2, 20480, 4, 255, 2), (20479, 15, 16384, 0, 0, 4), (24577, 16, 20481, 256, 256, 1),
     (41000, 17, 30000, 5, 1023, 3), (4096, 31, 1, 0, 0, 1), (4097, 64, 4096, 3, 1, 5), (6000, 127, 5000, 0, 100, 2),
     (9000, 511, 8000, 1, 0, 4), (9000, 512, 4000, 0, 7, 1), (9000, 513, 4000, 7, 0, 7), (300, 300, 150, 0, 0, 1),
-    (1024, 1, 600, 300, 300, 1)])
+    (1024, 1, 600, 300, 300, 1), (8317, 1040, 8192, 4, 0, 4), (8200, 2047, 8100, 0, 9, 3), (8200, 2049, 8000, 3, 0, 1),
+    (4000, 3999, 2000, 0, 0, 4), (12000, 380, 9000, 4, 64, 2), (40000, 1300, 16000, 16, 1000, 8)])
 def test_selection_edges(ds, n, runs, M, ns, nw, nb):
     """Lengths around a step of the selection (20480 slots), run counts around a run per wave, the lanes that share a
-    run's comparisons and the sorted ranking (from 513 on), budgets within and beyond the copy of the keep list."""
+    run's comparisons and the sorted ranking (from 513 on), short runs that share a wave (with a long one among them in
+    test_long_runs_among_short_ones), budgets within and beyond the copy of the keep list."""
     rng = np.random.default_rng(n + runs)
     cuts = np.sort(rng.choice(np.arange(1, n), runs - 1, replace=False))
     chunk = np.searchsorted(cuts, np.arange(n), side="right").astype(np.int32)
@@ -456,3 +458,59 @@ def test_one_violation_anywhere_leaves_the_cache_untouched(ds, n, at):
     assert ds.kv_device_status(ws)[0] == 1
     assert torch.equal(pos, p0) and torch.equal(chunk, c0) and torch.equal(slot, s0)
     assert bool((keep == -1).all()) and bool((free == -1).all())
+
+
+@pytest.mark.parametrize("n_long,long,n_short,short", [(1, 9000, 2000, 1), (3, 700, 900, 4), (40, 130, 1500, 3), (2, 33, 300, 4),
+                                                       (2, 32, 300, 4), (1, 20000, 1900, 2), (5, 300, 2500, 2)])
+def test_long_runs_among_short_ones(ds, n_long, long, n_short, short):
+    """Runs far from the average length, which whole waves write while groups of lanes write the others: first, last and in
+    the middle, evicted and kept."""
+    rng = np.random.default_rng(n_long + long)
+    lens = np.full(n_short + n_long, short)
+    lens[np.sort(rng.choice(len(lens), n_long, replace=False))] = long
+    if n_long > 1:
+        lens[0] = lens[-1] = long
+    chunk = np.repeat(np.arange(len(lens)), lens).astype(np.int32)
+    n = len(chunk)
+    pos = np.cumsum(rng.integers(1, 4, n)).astype(np.int32)
+    scores = rng.random(len(lens)).astype(np.float32)
+    for M in (n - 3, n // 2):
+        one_event(ds, 1, 8, chunk, pos, scores, M, 4, 0, 2)
+        indexed_event(ds, chunk, pos, scores, M, 0, min(50, M), 1, seed=3)
+
+
+def test_many_short_runs_take_their_share_of_the_time(ds):
+    """16509 slots in 2064 runs take 3.3 times as long to select from as in 258 runs (the ranking sorts 8 times as many);
+    with a whole wave a run it was 4.8 times."""
+    M, n = 16384, 16509
+    i = torch.arange(n, dtype=torch.int32, device=DEV)
+    ws = torch.empty(ds.kv_indexed_workspace_bytes(n), dtype=torch.uint8, device=DEV)
+    free = torch.empty(n - M, dtype=torch.int32, device=DEV)
+
+    def of(run):
+        chunk0 = i // run
+        scores = torch.rand(int(chunk0[-1]) + 1, generator=torch.Generator().manual_seed(1)).to(DEV)
+        pos, chunk, slot = i.clone(), chunk0.clone(), i.clone()
+
+        def restore():
+            pos.copy_(i), chunk.copy_(chunk0), slot.copy_(i)
+
+        def event():
+            restore()
+            ds.kv_evict_topk_indexed(pos, chunk, slot, scores, n, M, 4, 1024, 4, free_out=free, workspace=ws)
+
+        def per_call(f):
+            f()
+            best = float("inf")
+            for _ in range(5):
+                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                e0.record()
+                for _ in range(20):
+                    f()
+                e1.record()
+                e1.synchronize()
+                best = min(best, e0.elapsed_time(e1) / 20)
+            return best
+        return per_call(event) - per_call(restore)
+    few, many = of(64), of(8)
+    assert many <= 4.1 * few, (many, few)
