@@ -199,9 +199,16 @@ def gdn_layers_fwd(q, k, v, g, beta, T, state, o, drift_partials, workspace, sca
     pairs = H_v * (d // 16) if drift_per_slice else H_v
     if state.numel() != L * H_v * d * d or drift_partials.numel() != L * pairs * 2:
         raise ValueError("state or drift_partials of another size")
-    for t in (q, k, v, g, beta, state, o, drift_partials):
-        if not t.is_contiguous():
-            raise ValueError("every array must be contiguous")
+    bf16, f32 = torch.bfloat16, torch.float32
+    for t, dt in ((q, bf16), (k, bf16), (v, bf16), (g, f32), (beta, f32), (state, f32), (drift_partials, f32)):
+        if t.dtype is not dt or not t.is_contiguous():
+            raise ValueError("q, k, v must be contiguous bf16; g, beta, state and drift_partials contiguous fp32")
+    if o.dtype not in (bf16, f32) or not o.is_contiguous() or workspace.dtype is not torch.uint8 \
+            or not workspace.is_contiguous():
+        raise ValueError("o must be contiguous bf16 or fp32, workspace contiguous uint8")
+    dev = q.get_device()
+    if dev < 0 or any(t.get_device() != dev for t in (k, v, g, beta, state, o, drift_partials, workspace)):
+        raise ValueError("every array must be on the same GPU")
     shape = GdnShape(L, L * int(T), H_k, H_v, d, d, 0, L, int(bool(drift_per_slice)))
     od = DS_BF16 if o.dtype == torch.bfloat16 else DS_F32
     _check(lib().gdn_layers_fwd(ctypes.byref(shape), pitch, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
@@ -210,14 +217,29 @@ def gdn_layers_fwd(q, k, v, g, beta, T, state, o, drift_partials, workspace, sca
 
 
 def gdn_pack_layers(layer_inputs, T, packed, stream=None):
-    """The first T rows of every layer's (q, k, v, g, beta) into the packed arrays [L][pitch]... of gdn_layers_fwd."""
+    """The first T rows of every layer's (q, k, v, g, beta) into the packed arrays [L][pitch]... of gdn_layers_fwd.
+
+    Contiguous tensors of at least T rows, q, k, v in bf16 and g, beta in fp32, on one GPU.
+    """
     L, pitch, H_k, d = packed[0].shape
     H_v = packed[2].shape[2]
-    rows = [p.shape[2:] for p in packed]
+    bf16, f32 = torch.bfloat16, torch.float32
+    want = [(bf16, (H_k, d)), (bf16, (H_k, d)), (bf16, (H_v, d)), (f32, (H_v,)), (f32, (H_v,))]
+    if len(packed) != 5 or len(layer_inputs) != L or any(len(x) != 5 for x in layer_inputs):
+        raise ValueError("(q, k, v, g, beta) packed, and of each of its layers")
+    if any(p.dtype is not dt or p.shape != (L, pitch) + r or not p.is_contiguous() for p, (dt, r) in zip(packed, want)):
+        raise ValueError("the packed arrays are not contiguous (q, k, v, g, beta) of L layers at one pitch")
+    if not 0 < T <= pitch:
+        raise ValueError(f"{T} tokens at a pitch of {pitch}")
+    dev = packed[0].get_device()
     for x in layer_inputs:
-        for t, p, r in zip(x, packed, rows):
-            if t.element_size() != p.element_size() or t.shape[0] < T or t.shape[1:] != r:
-                raise ValueError("a layer's inputs are not (q, k, v, g, beta) of the session's heads")
+        for t, (dt, r) in zip(x, want):
+            if t.dtype is not dt or t.shape[0] < T or t.shape[1:] != r or not t.is_contiguous():
+                raise ValueError("a layer's inputs are not contiguous (q, k, v, g, beta) of the session's heads")
+            if t.get_device() != dev:
+                raise ValueError("a layer's inputs are on another device")
+    if dev < 0 or any(p.get_device() != dev for p in packed):
+        raise ValueError("every array must be on the same GPU")
     src = (ctypes.c_void_p * (5 * L))(*[x[i].data_ptr() for i in range(5) for x in layer_inputs])
     dst = (ctypes.c_void_p * 5)(*[p.data_ptr() for p in packed])
     _check(lib().gdn_pack_layers(L, int(T), pitch, H_k, H_v, d, src, dst, _stream(stream)))

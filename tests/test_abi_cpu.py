@@ -263,3 +263,65 @@ def test_append_host_checks(ds):
     assert call(slot=fake + 2) == 4
     assert b"int32 pointer" in L.ds_last_error()
     assert call(T=0, na=0, planes=None, rows=None) == 0
+
+
+def _packed(torch, L=2, T=4, H_k=1, H_v=2, d=64):
+    bf, f = torch.bfloat16, torch.float32
+    return [torch.zeros((L, T) + r, dtype=dt) for dt, r in ((bf, (H_k, d)), (bf, (H_k, d)), (bf, (H_v, d)), (f, (H_v,)),
+                                                           (f, (H_v,)))]
+
+
+def _refused(ds, fn, why, *args):
+    import types
+    with pytest.raises(ValueError, match=why):
+        fn(*args, stream=types.SimpleNamespace(cuda_stream=0))
+
+
+def test_pack_layers_refuses_what_its_kernel_would_misread(ds):
+    """gdn_pack_layers hands plain pointers to its kernel: rows of other types, layouts, shapes or devices are refused on
+    the host, before any launch."""
+    import torch
+    packed = _packed(torch)
+    ok = [tuple(p[l].clone() for p in packed) for l in range(2)]
+    swap = lambda i, t: [ok[0], ok[1][:i] + (t,) + ok[1][i + 1:]]  # noqa: E731
+    go = lambda x, why, T=4, p=packed: _refused(ds, ds.gdn_pack_layers, why, x, T, p)  # noqa: E731
+    go(swap(3, torch.zeros(1, 2).expand(4, 2)), "inputs are not")                    # rows of stride 0
+    go(swap(0, torch.zeros(64, 1, 4, dtype=torch.bfloat16).permute(2, 1, 0)), "inputs are not")
+    go(swap(2, torch.zeros(4, 4, 64, dtype=torch.bfloat16)[:, ::2]), "inputs are not")
+    go(swap(1, torch.zeros(4, 1, 64, dtype=torch.float16)), "inputs are not")
+    go(swap(4, torch.zeros(4, 2, dtype=torch.int32)), "inputs are not")
+    go(swap(3, torch.zeros(3, 2)), "inputs are not")                                 # too few rows
+    go(swap(2, torch.zeros(4, 1, 64, dtype=torch.bfloat16)), "inputs are not")
+    go(ok, "same GPU")                                                               # host memory
+    go(ok[:1], "of each of its layers")
+    go([ok[0], ok[1][:4]], "of each of its layers")
+    go(ok, "at a pitch", T=5)
+    go(ok, "at a pitch", T=0)
+    go(ok, "packed arrays are not", p=packed[:2] + [packed[2].half()] + packed[3:])
+    go(ok, "packed arrays are not", p=packed[:3] + [torch.zeros(2, 1, 2).expand(2, 4, 2)] + packed[4:])
+
+
+def test_layers_fwd_refuses_what_its_kernels_would_misread(ds):
+    """gdn_layers_fwd: arrays of other types, layouts, sizes or devices are refused on the host (an fp16 o would be written
+    past its end, an fp64 gate read as two)."""
+    import torch
+    q, k, v, g, beta = _packed(torch)
+    S, o, dp = torch.zeros(2, 1, 2, 64, 64), torch.zeros(2, 4, 2, 64), torch.zeros(2, 1, 2, 2)
+    ws = torch.empty(1 << 16, dtype=torch.uint8)
+    base = dict(q=q, k=k, v=v, g=g, beta=beta, T=4, state=S, o=o, drift_partials=dp, workspace=ws)
+
+    def go(why, **kw):
+        a = {**base, **kw}
+        _refused(ds, ds.gdn_layers_fwd, why, *[a[n] for n in ("q", "k", "v", "g", "beta", "T", "state", "o",
+                                                              "drift_partials", "workspace")])
+    go("contiguous", o=o.half())
+    go("contiguous", q=q.half())
+    go("contiguous", g=g.double())
+    go("contiguous", state=S.double())
+    go("contiguous", drift_partials=dp.double())
+    go("contiguous", beta=beta.transpose(0, 1).contiguous().transpose(0, 1))
+    go("contiguous", workspace=ws.float())
+    go("shape", o=o[:, :3])
+    go("another size", state=S[:1])
+    go("same GPU")
+    go("same GPU", o=o.to("meta"))

@@ -126,6 +126,10 @@ def test_refused_arguments(ds):
         ds.gdn_pack_layers(xs, 5, packed)
     with pytest.raises(ValueError):
         ds.gdn_pack_layers([x[:2] + (x[2][:, :1],) + x[3:] for x in xs], 4, packed)
+    with pytest.raises(ValueError, match="another device"):
+        ds.gdn_pack_layers([xs[0], xs[1][:3] + (xs[1][3].cpu(),) + xs[1][4:]], 4, packed)
+    with pytest.raises(ValueError, match="same GPU"):
+        ds.gdn_layers_fwd(*packed, 4, S, o.cpu(), p, ws)
 
 
 @pytest.mark.parametrize("form", ["contiguous", "slice", "strided", "host", "misaligned"])
