@@ -216,6 +216,26 @@ def gdn_layers_fwd(q, k, v, g, beta, T, state, o, drift_partials, workspace, sca
                                 _ptr(workspace), workspace.numel(), _stream(stream)))
 
 
+def _layer_rows(H_k, H_v, d):
+    """Type and row shape of q, k, v, g, beta."""
+    bf16, f32 = torch.bfloat16, torch.float32
+    return [(bf16, (H_k, d)), (bf16, (H_k, d)), (bf16, (H_v, d)), (f32, (H_v,)), (f32, (H_v,))]
+
+
+def check_layer_inputs(layer_inputs, T, H_k, H_v, d, dev):
+    """Raise ValueError unless every layer's (q, k, v, g, beta) are contiguous tensors of at least T rows on GPU `dev`
+    (an index), q, k, v in bf16 and g, beta in fp32."""
+    want = _layer_rows(H_k, H_v, d)
+    for x in layer_inputs:
+        if len(x) != 5:
+            raise ValueError("(q, k, v, g, beta) packed, and of each of its layers")
+        for t, (dt, r) in zip(x, want):
+            if t.dtype is not dt or t.shape[0] < T or t.shape[1:] != r or not t.is_contiguous():
+                raise ValueError("a layer's inputs are not contiguous (q, k, v, g, beta) of the session's heads")
+            if t.get_device() != dev:
+                raise ValueError("a layer's inputs are on another device")
+
+
 def gdn_pack_layers(layer_inputs, T, packed, stream=None):
     """The first T rows of every layer's (q, k, v, g, beta) into the packed arrays [L][pitch]... of gdn_layers_fwd.
 
@@ -223,21 +243,15 @@ def gdn_pack_layers(layer_inputs, T, packed, stream=None):
     """
     L, pitch, H_k, d = packed[0].shape
     H_v = packed[2].shape[2]
-    bf16, f32 = torch.bfloat16, torch.float32
-    want = [(bf16, (H_k, d)), (bf16, (H_k, d)), (bf16, (H_v, d)), (f32, (H_v,)), (f32, (H_v,))]
-    if len(packed) != 5 or len(layer_inputs) != L or any(len(x) != 5 for x in layer_inputs):
+    dev = packed[0].get_device()
+    want = _layer_rows(H_k, H_v, d)
+    if len(packed) != 5 or len(layer_inputs) != L:
         raise ValueError("(q, k, v, g, beta) packed, and of each of its layers")
     if any(p.dtype is not dt or p.shape != (L, pitch) + r or not p.is_contiguous() for p, (dt, r) in zip(packed, want)):
         raise ValueError("the packed arrays are not contiguous (q, k, v, g, beta) of L layers at one pitch")
     if not 0 < T <= pitch:
         raise ValueError(f"{T} tokens at a pitch of {pitch}")
-    dev = packed[0].get_device()
-    for x in layer_inputs:
-        for t, (dt, r) in zip(x, want):
-            if t.dtype is not dt or t.shape[0] < T or t.shape[1:] != r or not t.is_contiguous():
-                raise ValueError("a layer's inputs are not contiguous (q, k, v, g, beta) of the session's heads")
-            if t.get_device() != dev:
-                raise ValueError("a layer's inputs are on another device")
+    check_layer_inputs(layer_inputs, T, H_k, H_v, d, dev)
     if dev < 0 or any(p.get_device() != dev for p in packed):
         raise ValueError("every array must be on the same GPU")
     src = (ctypes.c_void_p * (5 * L))(*[x[i].data_ptr() for i in range(5) for x in layer_inputs])

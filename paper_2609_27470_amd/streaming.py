@@ -47,13 +47,14 @@ from dataclasses import dataclass
 
 import torch
 
-from . import (LAYER_FROB, deltas_drift, gdn_layers_fwd, gdn_pack_layers, gdn_shape, gdn_workspace_bytes,
+from . import (LAYER_FROB, check_layer_inputs, deltas_drift, gdn_layers_fwd, gdn_pack_layers, gdn_shape, gdn_workspace_bytes,
                kv_append_indexed, kv_evict_topk, kv_evict_topk_indexed, kv_indexed_workspace_bytes, kv_outcome_word,
                kv_workspace_bytes)
 
-# at most this much workspace for the layers that one call takes together (76 MiB for 24 layers of 32 heads and 132
-# tokens; sessions of much longer chunks run their layers in groups, each of which fills the GPU by itself)
-LAYERS_WORKSPACE = 1 << 30
+# at most this much workspace for the layers that one call takes together, unless a session is given another bound (76
+# MiB for 24 layers of 32 heads and 132 tokens; sessions of much longer chunks run their layers in groups, each of which
+# fills the GPU by itself)
+LAYERS_WORKSPACE = 256 << 20
 
 
 class EvictionFailed(RuntimeError):
@@ -88,12 +89,15 @@ class DeltaSStream:
     token; budget M tokens, cache capacity M + max_chunk; the policy's sink,
     window and span counts (the paper uses 4, 1024 and 4).  `o` holds every
     linear-attention layer's output of the latest chunk ([layer][token]
-    [H_v][d] in o_dtype).
+    [H_v][d] in o_dtype).  layers_workspace bounds the workspace (bytes) of the
+    layers that run in one call (default LAYERS_WORKSPACE; one layer's at least);
+    `step` copies the inputs of as many layers at a time, into buffers that the
+    session holds from the start.
     """
 
     def __init__(self, n_layers, H_k, H_v, d, kv_layers, row_elems, M, max_chunk, max_chunks,
                  n_sink=4, n_window=1024, n_buckets=4, score_mode=LAYER_FROB, device="cuda", indexed=True,
-                 o_dtype=torch.bfloat16):
+                 o_dtype=torch.bfloat16, layers_workspace=None):
         if n_sink + n_window > M:
             raise ValueError("sink + window exceed the budget")
         dev = torch.device(device)
@@ -116,12 +120,14 @@ class DeltaSStream:
         self.chunk_id = torch.zeros(self.capacity, dtype=torch.int32, device=dev)
         self.scores = torch.zeros(max_chunks, dtype=torch.float32, device=dev)
         need = lambda n: gdn_workspace_bytes(gdn_shape([max_chunk] * n, H_k, H_v, d, 0))  # noqa: E731
+        bound = LAYERS_WORKSPACE if layers_workspace is None else layers_workspace
         self.group = n_layers   # layers per call
-        while self.group > 1 and not 0 < need(self.group) <= LAYERS_WORKSPACE:   # (0: too large for one call)
+        while self.group > 1 and not 0 < need(self.group) <= bound:   # (0: too large for one call)
             self.group = (self.group + 1) // 2
         rest = n_layers % self.group
         self.gdn_ws = torch.empty(max(need(self.group), need(rest) if rest else 0, 1), dtype=torch.uint8, device=dev)
-        self.inputs = self._packed = None
+        self.inputs = None
+        self._packed = self._input_buffers(torch.empty, self.group)
         self.indexed = indexed
         if indexed:
             self.slot = torch.zeros(self.capacity, dtype=torch.int32, device=dev)
@@ -180,10 +186,13 @@ class DeltaSStream:
             raise ValueError("score table full")
         # every launch and copy of the step on one stream (the caller's, else the current one)
         with _on(stream):
-            if self._packed is None:
-                self._packed = self._input_buffers(torch.empty)
-            gdn_pack_layers(layer_inputs, T, self._packed)
-            self._layers(T, self._packed)
+            if self.group < self.L:   # a layer of a later group is refused before the first one runs
+                check_layer_inputs(layer_inputs, T, self.H_k, self.H_v, self.d, self.state.get_device())
+            for a in range(0, self.L, self.group):
+                x = [t[:self.L - a] for t in self._packed]
+                gdn_pack_layers(layer_inputs[a:a + self.group], T, x)
+                self._layers(T, a, x)
+            self._score()
             return self._append_and_evict(T, k_rows, v_rows)
 
     def check(self):
@@ -244,24 +253,25 @@ class DeltaSStream:
         idx = self.slot[:n].to(torch.int64)
         return self.k[:, idx], self.v[:, idx]
 
-    def _input_buffers(self, make):
-        L, Tm, dev = self.L, self.max_chunk, self.dev
+    def _input_buffers(self, make, L):
+        Tm, dev = self.max_chunk, self.dev
         new = lambda dt, *s: make((L, Tm) + s, dtype=dt, device=dev)  # noqa: E731
         return (new(torch.bfloat16, self.H_k, self.d), new(torch.bfloat16, self.H_k, self.d),
                 new(torch.bfloat16, self.H_v, self.d), new(torch.float32, self.H_v), new(torch.float32, self.H_v))
 
     def capture_graph(self):
         """Allocate the input buffers (q, k, v, g, beta, each [layer][max_chunk]...) of step_inputs."""
-        self.inputs = self._input_buffers(torch.zeros)
+        self.inputs = self._input_buffers(torch.zeros, self.L)
 
-    def _layers(self, T, x):
-        """Every layer over the first T tokens of x, then the chunk's score."""
+    def _layers(self, T, a, x):
+        """The layers from a on that x holds, over the first T tokens of x."""
+        b = a + x[0].shape[0]
+        gdn_layers_fwd(*x, T, self.state[a:b], self.o[a:b], self.partials[a:b], self.gdn_ws,
+                       drift_per_slice=self.per_slice)
+
+    def _score(self):
+        """The chunk's score from the drift sums of its layers."""
         c = self.n_chunks
-        for a in range(0, self.L, self.group):
-            q, k, v, g, beta = x if self.group == self.L else (t[a:a + self.group] for t in x)
-            b = a + self.group
-            gdn_layers_fwd(q, k, v, g, beta, T, self.state[a:b], self.o[a:b], self.partials[a:b], self.gdn_ws,
-                           drift_per_slice=self.per_slice)
         deltas_drift(self.partials, self.score_mode, scores=self.scores[c:c + 1])
 
     def step_inputs(self, T, k_rows, v_rows):
@@ -274,7 +284,9 @@ class DeltaSStream:
             raise ValueError(f"chunk of {T} tokens (1..{self.max_chunk})")
         if self.n_chunks >= self.scores.numel():
             raise ValueError("score table full")
-        self._layers(T, self.inputs)
+        for a in range(0, self.L, self.group):
+            self._layers(T, a, [t[a:a + self.group] for t in self.inputs])
+        self._score()
         return self._append_and_evict(T, k_rows, v_rows)
 
     def save(self) -> Snapshot:

@@ -154,3 +154,52 @@ def test_rows_of_every_layout_join_the_contiguous_cache(ds, form):
     n = 4 * T
     assert s.length == n and torch.equal(s.k[:, :n], want) and torch.equal(s.v[:, :n], want)
     assert s.pos[:n].tolist() == list(range(n)) and s.chunk_id[:n].tolist() == [i // T for i in range(n)]
+
+
+def test_first_step_allocates_nothing_and_can_be_captured(ds):
+    """The buffers of step are there from the start: the first step allocates no device memory, and captured into a graph
+    it gives the chunk that the eager session gives."""
+    from paper_2609_27470_amd.streaming import DeltaSStream
+    L, H_k, H_v, d, T = 5, 2, 4, 64, 50
+    new = lambda: DeltaSStream(L, H_k, H_v, d, 1, 64, 256, 80, 16, 4, 64, 2, device=DEV)  # noqa: E731
+    a, b, c = new(), new(), new()
+    rows, xs = torch.randint(-99, 99, (1, T, 64), dtype=torch.int16, device=DEV), layers(L, T, H_k, H_v, d)
+    torch.cuda.synchronize()
+    count = lambda: torch.cuda.memory_stats()["allocation.all.allocated"]  # noqa: E731
+    before = count()
+    a.step(xs, rows, rows)
+    assert count() == before
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b.step(xs, rows, rows)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(a.state, b.state) and torch.equal(a.o[:, :T], b.o[:, :T]) and torch.equal(a.scores[:1], b.scores[:1])
+    assert torch.equal(a.k, b.k) and torch.equal(a.pos, b.pos) and a.length == b.length
+    bad = xs[:4] + [xs[4][:1] + (xs[4][1].half(),) + xs[4][2:]]
+    with pytest.raises(ValueError):
+        c.step(bad, rows, rows)
+    assert bool((c.state == 0).all()) and c.n_chunks == 0
+
+
+def test_workspace_bound_of_a_session(ds):
+    """layers_workspace bounds what the layers of one call take together, and the copy of their inputs with it; a later
+    group's input is refused before the first group runs."""
+    from paper_2609_27470_amd.streaming import DeltaSStream
+    L, H_k, H_v, d, T = 5, 2, 4, 64, 50
+    new = lambda **kw: DeltaSStream(L, H_k, H_v, d, 1, 64, 256, 80, 16, 4, 64, 2, device=DEV, **kw)  # noqa: E731
+    need = lambda n: ds.gdn_workspace_bytes(ds.gdn_shape([80] * n, H_k, H_v, d, 0))  # noqa: E731
+    rows, xs = torch.zeros(1, T, 64, dtype=torch.int16, device=DEV), layers(L, T, H_k, H_v, d)
+    whole = new()
+    whole.step(xs, rows, rows)
+    for bound, group in ((need(5), 5), (need(5) - 1, 3), (need(2), 2), (need(1), 1), (0, 1)):
+        s = new(layers_workspace=bound)
+        assert s.group == group and s.gdn_ws.numel() <= max(bound, need(1)) and s._packed[0].shape[0] == group
+        s.step(xs, rows, rows)
+        assert torch.equal(s.state, whole.state) and torch.equal(s.o[:, :T], whole.o[:, :T])
+        assert torch.equal(s.scores[:1], whole.scores[:1])
+        s2 = new(layers_workspace=bound)
+        with pytest.raises(ValueError):
+            s2.step(xs[:4] + [xs[4][:3] + (xs[4][3][:, :1].expand(T, H_v),) + xs[4][4:]], rows, rows)
+        assert bool((s2.state == 0).all())
