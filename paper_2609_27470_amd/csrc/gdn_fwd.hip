@@ -1314,6 +1314,8 @@ hipError_t launch_gdn_pack(const GdnPack &p, int n_layers, hipStream_t stream) {
 }
 
 hipError_t launch_gdn(const GdnLaunch &p, hipStream_t stream) {
+    // the write signal's rows are T_total tokens long, which Streams does not hold at a pitch
+    if (p.pitch && p.write_partials) return hipErrorInvalidValue;
     if (p.d == 128) return launch_d<128>(p, stream);
     return launch_d<64>(p, stream);
 }

@@ -203,3 +203,32 @@ def test_workspace_bound_of_a_session(ds):
         with pytest.raises(ValueError):
             s2.step(xs[:4] + [xs[4][:3] + (xs[4][3][:, :1].expand(T, H_v),) + xs[4][4:]], rows, rows)
         assert bool((s2.state == 0).all())
+
+
+@pytest.mark.parametrize("per_slice", [True, False])
+@pytest.mark.parametrize("L,T,pitch,H_k,H_v,d,frame_len", [
+    (3, 200, 210, 2, 4, 64, 64), (4, 130, 130, 2, 4, 128, 128),        # per-slice kernel
+    (16, 300, 333, 2, 4, 128, 64), (20, 64, 100, 2, 4, 128, 64),       # half heads
+    (40, 257, 300, 2, 4, 128, 64), (9, 129, 132, 8, 16, 128, 128)])    # whole heads, as a call that may be split
+def test_frames_at_a_pitch(ds, L, T, pitch, H_k, H_v, d, frame_len, per_slice):
+    """The C entry takes frames of any length: each layer's frames, numbered layer by layer, are those of its own call."""
+    import ctypes
+    xs = layers(L, T, H_k, H_v, d, seed=7)
+    S0 = 0.3 * torch.randn(L, H_v, d, d, device=DEV)
+    packed = packed_like(ds, xs, T, pitch)
+    F, pairs = -(-T // frame_len), H_v * (d // 16) if per_slice else H_v
+    o, S = torch.full((L, pitch, H_v, d), 5.0, device=DEV), torch.empty_like(S0)
+    room = L * T // frame_len + L     # frames that so many tokens may hold: those not reached read zero
+    p = torch.full((room, pairs, 2), float("nan"), device=DEV)
+    shape = ds.GdnShape(L, L * T, H_k, H_v, d, d, frame_len, room, int(per_slice))
+    ws = torch.empty(ds.gdn_workspace_bytes(shape), dtype=torch.uint8, device=DEV)
+    P = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    rc = ds.lib().gdn_layers_fwd(ctypes.byref(shape), pitch, *[P(t) for t in packed], P(S0), P(S), P(o), ds.DS_F32, 1.0, P(p),
+                                 P(ws), ws.numel(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert rc == 0
+    for l, x in enumerate(xs):
+        r = ds.gdn_chunk_fwd(*x, [T], frame_len, state_in=S0[l:l + 1].contiguous(), drift_per_slice=per_slice)
+        assert rel(o[l, :T], r["o"]) <= 5e-5 and rel(S[l], r["state"][0]) <= 5e-5, l
+        assert rel(p[l * F:(l + 1) * F], r["drift_partials"]) <= 1e-4, l
+    assert bool((p[L * F:] == 0).all()) and bool((o[:, T:] == 5).all())
