@@ -210,8 +210,10 @@ def streaming_bench(ds, dev, stream, n_chunks, n_layers=24):
     v_rows = torch.randint(-2000, 2000, (KV_LAYERS, 132, row_elems), dtype=torch.int16, device=dev, generator=gen)
     state_io = n_layers * 2 * H_V * D * D * 4   # every layer reads and writes its state once per chunk
     out = {"layers": n_layers, "policy": "n_sink=4, n_window=1024, N=4", "state_io_bytes_per_chunk": state_io}
-    runs = [(BUDGET, "eager"), (BUDGET, "graph"), (BUDGET, "graph_indexed"), (8192, "eager"),
-            (8192, "graph_indexed")]
+    # step (separate tensors per layer) or step_inputs (the session's input buffers); the cache whose rows are compacted,
+    # or the slot-indexed one
+    runs = [(BUDGET, "step"), (BUDGET, "inputs"), (BUDGET, "inputs_indexed"), (8192, "step"),
+            (8192, "inputs_indexed")]
     for M, mode in runs:
         s = DeltaSStream(n_layers, H_K, H_V, D, KV_LAYERS, row_elems, M, 132, M // 128 + total + 8,
                          4, 1024, 4, device=dev, indexed=mode.endswith("indexed"))
@@ -223,7 +225,7 @@ def streaming_bench(ds, dev, stream, n_chunks, n_layers=24):
         if s.indexed:
             s.slot[:M] = torch.arange(M, dtype=torch.int32, device=dev)
             s.free = torch.arange(M, s.capacity, dtype=torch.int32, device=dev)
-        if mode.startswith("graph"):
+        if mode.startswith("inputs"):
             s.capture_graph()
         off = 0
         evs = []
@@ -235,7 +237,7 @@ def streaming_bench(ds, dev, stream, n_chunks, n_layers=24):
                 e = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
                 e[0].record(stream)
                 h0 = time.perf_counter()
-            if mode == "eager":
+            if mode == "step":
                 e[1].record(stream) if timed else None
                 s.step([tuple(x[l, a:a + Tc] for x in pools) for l in range(n_layers)],
                        k_rows[:, :Tc], v_rows[:, :Tc])

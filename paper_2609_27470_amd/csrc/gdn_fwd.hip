@@ -1213,9 +1213,9 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     // (1024-token calls: 13.4 -> see the kernel trace; one streamed chunk:
     // 11.2 -> 8.6 us).  Longer calls share the Gram products of a qk-head.
     a.prep_per_vhead = a.group > 1 && (long long)p.tiles_max * p.H_v <= 1024;
-    // calls of at most two tiles on the per-slice kernel (most streamed chunks)
-    // form their prep inside it: one launch per layer, 16.1 instead of 18.4 us
-    // a layer at 24 layers x 128 tokens.  (With three tiles a second prep round,
+    // calls of at most two tiles on the per-slice kernel (one layer over a chunk)
+    // form their prep inside it: one launch, 16.1 instead of 18.4 us at 128 tokens
+    // x 32 heads.  (With three tiles a second prep round,
     // or a third group of waves, costs what the launch saves.)  Not with the
     // per-head drift sums, whose slice counters the prep pass clears before any
     // sequential workgroup runs.

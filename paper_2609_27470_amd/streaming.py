@@ -21,11 +21,12 @@ copies are plain device copies.
 A chunk is a tiny call per layer (about 125 tokens) that leaves most of the GPU
 idle, and the inputs of all layers are there before the first one runs: the
 layers go through `gdn_layers_fwd` together (24 layers x 125 tokens x 32 heads,
-append and eviction included: 115 us a chunk; with a launch per layer, replayed
+append and eviction included: 117 us a chunk; with a launch per layer, replayed
 as a HIP graph, 434 us).
-`capture_graph` allocates input buffers in that call's layout (`inputs`);
-`step_inputs` runs a chunk that the caller has written there, `step` first
-brings separate per-layer tensors into such a layout of its own.
+`capture_graph` allocates input buffers in that call's layout (`inputs`; nothing is
+captured, the name is that of the graph it once recorded); `step_inputs` runs a
+chunk that the caller has written there, `step` first brings separate per-layer
+tensors into such a layout of its own.
 
 By default (`indexed=True`) the cache is addressed through a slot table
 (logical token i lives in physical row slot[i]): eviction is
@@ -201,7 +202,7 @@ class DeltaSStream:
         code = int(self.kv_fail.item())
         if code != 0:
             raise EvictionFailed(f"an eviction reported outcome {code} (1: cache invariants broken, "
-                                 "2: keep count wrong, 3: gather wait timed out)")
+                                 "2: keep count wrong)")
 
     def _appendable(self, rows, T):
         """Whether kv_append_indexed can read the chunk's rows as they are (other types, layouts and devices go
