@@ -79,11 +79,11 @@ size_t ds_gdn_write_workspace_bytes(const ds_gdn_shape *shape) {
 }
 
 // gdn_chunk_fwd, gdn_chunk_fwd_longest (pitch 0) and gdn_layers_fwd (longest 0)
-static ds_status gdn_forward(const ds_gdn_shape *shape, int32_t longest, int32_t pitch, const void *q, const void *k, const void *v,
-                             const float *g, const float *beta, const int32_t *cu_seqlens, const float *state_in,
-                             float *state_out, void *o, int32_t o_dtype, float scale, float *drift_partials,
-                             float *write_partials, float *snapshots, void *workspace, size_t workspace_bytes,
-                             void *stream) {
+static ds_status gdn_forward(const ds_gdn_shape *shape, int32_t longest, int32_t pitch, const void *q,
+                             const void *k, const void *v, const float *g, const float *beta,
+                             const int32_t *cu_seqlens, const float *state_in, float *state_out, void *o,
+                             int32_t o_dtype, float scale, float *drift_partials, float *write_partials,
+                             float *snapshots, void *workspace, size_t workspace_bytes, void *stream) {
     ds_status st = check_gdn_shape(shape);
     if (st != DS_OK) return st;
     const ds_gdn_shape &s = *shape;
@@ -179,8 +179,8 @@ ds_status gdn_layers_fwd(const ds_gdn_shape *shape, int32_t pitch, const void *q
         return fail(DS_E_SHAPE, "pitch=%d is less than the %d tokens of a layer", pitch, shape->T_total / shape->B);
     if (shape->H_v >= 1 && (long long)pitch * shape->B > (1LL << 30) / shape->H_v)
         return fail(DS_E_UNSUPPORTED, "problem too large for one call");
-    return gdn_forward(shape, 0, pitch, q, k, v, g, beta, nullptr, state_in, state_out, o, o_dtype, scale, drift_partials,
-                       nullptr, nullptr, workspace, workspace_bytes, stream);
+    return gdn_forward(shape, 0, pitch, q, k, v, g, beta, nullptr, state_in, state_out, o, o_dtype, scale,
+                       drift_partials, nullptr, nullptr, workspace, workspace_bytes, stream);
 }
 
 ds_status gdn_pack_layers(int32_t n_layers, int32_t T, int32_t pitch, int32_t H_k, int32_t H_v, int32_t d,

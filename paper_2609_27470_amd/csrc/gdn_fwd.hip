@@ -1151,7 +1151,8 @@ GdnWorkspace gdn_workspace_layout(int B, int T_total, int H_k, int H_v, int d, i
     w.offP = off;
     off = align256(off + (size_t)w.tiles_max * H_v * TP_HALVES * sizeof(_Float16));
     w.offQ = off;  // fp16 q fragments, only for the per-slice kernel
-    if (!use_wide(B, H_v, d) || (long long)B * H_v < WIDE_FORMS_P) off = align256(off + (size_t)w.tiles_max * H_k * 64 * d * sizeof(_Float16));
+    if (!use_wide(B, H_v, d) || (long long)B * H_v < WIDE_FORMS_P)
+        off = align256(off + (size_t)w.tiles_max * H_k * 64 * d * sizeof(_Float16));
     w.offGam = off;
     off = align256(off + (size_t)w.tiles_max * H_v * 128 * sizeof(float));
     w.offDrift = off;
@@ -1215,10 +1216,9 @@ static hipError_t launch_d(const GdnLaunch &p, hipStream_t stream) {
     a.prep_per_vhead = a.group > 1 && (long long)p.tiles_max * p.H_v <= 1024;
     // calls of at most two tiles on the per-slice kernel (one layer over a chunk)
     // form their prep inside it: one launch, 16.1 instead of 18.4 us at 128 tokens
-    // x 32 heads.  (With three tiles a second prep round,
-    // or a third group of waves, costs what the launch saves.)  Not with the
-    // per-head drift sums, whose slice counters the prep pass clears before any
-    // sequential workgroup runs.
+    // x 32 heads.  (With three tiles a second prep round, or a third group of
+    // waves, costs what the launch saves.)  Not with the per-head drift sums, whose
+    // slice counters the prep pass clears before any sequential workgroup runs.
     const bool one_launch = !wide && p.tiles_max > 0 && p.tiles_max <= 2 && !fused_drift;
     if (p.tiles_max > 0 && !one_launch) {
         // tiles rounded up to a multiple of 8 (workgroups past the last tile exit)

@@ -36,10 +36,10 @@
 // 32 heads on half heads, which would each form the head's P, 368 -> 348.)
 //
 // The state at a frame's start, needed for ||S_end - S_start||^2, is kept in a
-// scratch area of the workspace (64 KiB per head) rather than in registers, and read back at the
-// frame's end; for the first frame of a launch it is read from state_in again (an
-// empty buffer, which reads as zeros, without one), and nothing is kept once no
-// frame follows.  (The copies were a third of the traffic of a short call: one chunk
+// scratch area of the workspace (64 KiB per head) rather than in registers, and
+// read back at the frame's end; for the first frame of a launch it is read from
+// state_in again (an empty buffer, which reads as zeros, without one), and nothing
+// is kept once no frame follows.  (The copies were a third of the traffic of a short call: one chunk
 // of 125 tokens through 24 layers of 32 heads, with its append and eviction, 127 ->
 // 115 us.)
 //
@@ -822,7 +822,7 @@ static hipError_t launch_wide_nsl(const GdnArgs &a, int n_wg, bool o_bf16, bool 
 
 // Half heads throughout, in one launch, when two workgroups per head do not
 // outnumber the compute units (4 streams of 6151, 4097, 8190 and 5333 tokens
-// with 32 heads: 467 us a call on the per-slice kernel, 368 here).  Otherwise
+// with 32 heads: 463 us a call on the per-slice kernel, 346 here).  Otherwise
 // one launch of whole heads, or, for calls whose frames are whole tiles and
 // when at most tail_streams streams fill the GPU as half heads, whole heads up
 // to the cut (the tile from which at most tail_streams streams are left,
