@@ -1104,11 +1104,23 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // 2048, 1024) 305 and 300, 66 355 and 335, 82 613 and 499; slices and whole heads: 63
 // 915 and 936, 66 433 and 434 (459 without frames), 70 523 and 492 (538), 76 149 and
 // 136, 81 786 and 676 (731).  Without the longest stream's length the slices.
+// A frame end in between costs the whole-head kernel 1.6 us (the state goes to the
+// workspace and comes back), the slices, which keep it in registers, next to
+// nothing: frames of one tile want 35 - 50 more live heads for half heads and 95 for
+// whole ones, frames of two 25 and 24, of four 13 and 6.  Slices and the other, us, at frames of 64, 256 and 1024 tokens: one
+// stream of 4096 x 64 heads 167 and 195, 153 and 164, 151 and 146; mean 75 (8192,
+// 8000 and 3000 tokens x 32) 390 and 461, 373 and 369, 372 and 323; 91 (8 streams of
+// 16) 467 and 484, 447 and 390, 443 and 340; whole heads, mean 130 368 and 386, 350
+// and 274, 347 and 240; 160 (one stream of 2048) 236 and 245, 227 and 171, 223 and
+// 134.  One stream of 65 to 128 heads takes half heads at any frames: the slices of
+// more than 64 do not fit the CUs at once (2048 tokens, frames of 64 and 512: 66 heads
+// 198 and 193 us on slices, 114 and 90 on half heads, 96 135 and 125, 117 and 92).
 // Calls of at most WIDE_SMALL tokens are level or faster on half or whole heads
 // whatever the lengths (254 and 2 tokens x 32 heads 23.4 and 22.0, twice 1 token
 // 22.6 and 15.8).
 constexpr int WIDE_MIN_HEADS = 64;
-constexpr int WIDE_LIVE_HALF = 62, WIDE_LIVE_WHOLE = 72;
+constexpr int WIDE_LIVE_HALF = 60, WIDE_LIVE_WHOLE = 72;       // live heads wanted,
+constexpr int WIDE_FRAME_HALF = 48, WIDE_FRAME_WHOLE = 95;     // and more with a frame end at every tile
 constexpr int WIDE_SMALL = 256;
 // calls whose workspace has what the whole-head kernel needs
 static bool use_wide(int B, int H_v, int d) { return d == 128 && (long long)B * H_v >= WIDE_MIN_HEADS; }
@@ -1135,10 +1147,17 @@ static int device_cus() {
 // The whole-head kernel for this call (with tokens), or the per-slice one.
 static bool takes_wide(const GdnLaunch &p) {
     if (!use_wide(p.B, p.H_v, p.d) || p.tiles_max == 0) return false;
-    const int heads = p.B * p.H_v;
-    if (p.B == 1 || p.pitch || heads >= WIDE_FORMS_P || p.T_total <= WIDE_SMALL) return true;
-    const int live = 2 * heads <= device_cus() ? WIDE_LIVE_HALF : WIDE_LIVE_WHOLE;
-    return p.longest > 0 && (long long)p.T_total * p.H_v >= (long long)p.longest * live;
+    const int heads = p.B * p.H_v, longest = p.B == 1 || p.pitch ? p.T_total / p.B : p.longest;
+    if (heads >= WIDE_FORMS_P || p.T_total <= WIDE_SMALL) return true;
+    if (longest <= 0) return false;
+    const bool half = 2 * heads <= device_cus();
+    if (half && p.B == 1 && heads > WIDE_MIN_HEADS) return true;
+    double want = half ? WIDE_LIVE_HALF : WIDE_LIVE_WHOLE;
+    if (p.frame_len > 0 && (p.drift_partials || p.snapshots)) {
+        const double ends = (double)((longest - 1) / p.frame_len) / ((longest + 63) / 64);  // frame ends in between, per tile
+        want += half ? WIDE_FRAME_HALF * ends : WIDE_FRAME_WHOLE * ends * ends;
+    }
+    return (double)p.T_total * p.H_v >= want * longest;
 }
 
 GdnWorkspace gdn_workspace_layout(int B, int T_total, int H_k, int H_v, int d, int n_frames, bool with_write) {
