@@ -190,8 +190,8 @@ class DeltaSStream:
             if self.group < self.L:   # a layer of a later group is refused before the first one runs
                 check_layer_inputs(layer_inputs, T, self.H_k, self.H_v, self.d, self.state.get_device())
             for a in range(0, self.L, self.group):
-                x = [t[:self.L - a] for t in self._packed]
-                gdn_pack_layers(layer_inputs[a:a + self.group], T, x)
+                x = self._packed if self.L - a >= self.group else [t[:self.L - a] for t in self._packed]
+                gdn_pack_layers(layer_inputs if self.group == self.L else layer_inputs[a:a + self.group], T, x)
                 self._layers(T, a, x)
             self._score()
             return self._append_and_evict(T, k_rows, v_rows)
@@ -266,9 +266,10 @@ class DeltaSStream:
 
     def _layers(self, T, a, x):
         """The layers from a on that x holds, over the first T tokens of x."""
-        b = a + x[0].shape[0]
-        gdn_layers_fwd(*x, T, self.state[a:b], self.o[a:b], self.partials[a:b], self.gdn_ws,
-                       drift_per_slice=self.per_slice)
+        out = self.state, self.o, self.partials
+        if self.group < self.L:
+            out = [t[a:a + x[0].shape[0]] for t in out]
+        gdn_layers_fwd(*x, T, *out, self.gdn_ws, drift_per_slice=self.per_slice)
 
     def _score(self):
         """The chunk's score from the drift sums of its layers."""
@@ -286,7 +287,7 @@ class DeltaSStream:
         if self.n_chunks >= self.scores.numel():
             raise ValueError("score table full")
         for a in range(0, self.L, self.group):
-            self._layers(T, a, [t[a:a + self.group] for t in self.inputs])
+            self._layers(T, a, self.inputs if self.group == self.L else [t[a:a + self.group] for t in self.inputs])
         self._score()
         return self._append_and_evict(T, k_rows, v_rows)
 
