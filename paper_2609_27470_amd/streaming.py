@@ -26,7 +26,7 @@ as a HIP graph, 434 us).
 `capture_graph` allocates input buffers in that call's layout (`inputs`; nothing is
 captured, the name is that of the graph it once recorded); `step_inputs` runs a
 chunk that the caller has written there, `step` first brings separate per-layer
-tensors into such a layout of its own.
+tensors into such a layout of its own (the only layer of a session stays where it is).
 
 By default (`indexed=True`) the cache is addressed through a slot table
 (logical token i lives in physical row slot[i]): eviction is
@@ -48,14 +48,27 @@ from dataclasses import dataclass
 
 import torch
 
-from . import (LAYER_FROB, check_layer_inputs, deltas_drift, gdn_layers_fwd, gdn_pack_layers, gdn_shape, gdn_workspace_bytes,
-               kv_append_indexed, kv_evict_topk, kv_evict_topk_indexed, kv_indexed_workspace_bytes, kv_outcome_word,
-               kv_workspace_bytes)
+from . import (LAYER_FROB, check_layer_inputs, deltas_drift, gdn_chunk_fwd, gdn_layers_fwd, gdn_pack_layers, gdn_shape,
+               gdn_workspace_bytes, kv_append_indexed, kv_evict_topk, kv_evict_topk_indexed, kv_indexed_workspace_bytes,
+               kv_outcome_word, kv_workspace_bytes)
 
-# at most this much workspace for the layers that one call takes together, unless a session is given another bound (76
-# MiB for 24 layers of 32 heads and 132 tokens; sessions of much longer chunks run their layers in groups, each of which
-# fills the GPU by itself)
-LAYERS_WORKSPACE = 256 << 20
+# at most this much workspace for the layers that one call takes together, and as much for the copy of their inputs that
+# step makes, unless a session is given another bound (76 and 53 MB for 24 layers of 32 heads and 132 tokens; sessions of
+# much longer chunks run their layers in groups, each of which fills the GPU by itself)
+LAYERS_WORKSPACE = 1 << 30
+CUS = 256   # compute units: heads that run at once where each takes a workgroup
+
+
+def layers_per_call(n_layers, H_v, need, copy_bytes, bound):
+    """How many layers go through one call: as many as keep the workspace need(n) and the copies n * copy_bytes within the
+    bound (one at least), in calls of about equal size that fill the GPU the fewest times (24 layers of 32 heads by
+    eights rather than by twelves).  need(n) is 0 where n layers are too many for one call."""
+    most = 1
+    while most < n_layers and 0 < need(most + 1) <= bound and (most + 1) * copy_bytes <= bound:
+        most += 1
+    size = lambda calls: -(-n_layers // calls)  # noqa: E731
+    calls = min(range(size(most), n_layers + 1), key=lambda c: (c * -(-size(c) * H_v // CUS), c))
+    return size(calls)
 
 
 class EvictionFailed(RuntimeError):
@@ -91,9 +104,9 @@ class DeltaSStream:
     window and span counts (the paper uses 4, 1024 and 4).  `o` holds every
     linear-attention layer's output of the latest chunk ([layer][token]
     [H_v][d] in o_dtype).  layers_workspace bounds the workspace (bytes) of the
-    layers that run in one call (default LAYERS_WORKSPACE; one layer's at least);
-    `step` copies the inputs of as many layers at a time, into buffers that the
-    session holds from the start.
+    layers that run in one call, and the copy of their inputs that `step` makes into
+    buffers which the session holds from the start (default LAYERS_WORKSPACE; one
+    layer at a time at least, which needs no copy).
     """
 
     def __init__(self, n_layers, H_k, H_v, d, kv_layers, row_elems, M, max_chunk, max_chunks,
@@ -122,13 +135,12 @@ class DeltaSStream:
         self.scores = torch.zeros(max_chunks, dtype=torch.float32, device=dev)
         need = lambda n: gdn_workspace_bytes(gdn_shape([max_chunk] * n, H_k, H_v, d, 0))  # noqa: E731
         bound = LAYERS_WORKSPACE if layers_workspace is None else layers_workspace
-        self.group = n_layers   # layers per call
-        while self.group > 1 and not 0 < need(self.group) <= bound:   # (0: too large for one call)
-            self.group = (self.group + 1) // 2
+        copy_bytes = max_chunk * (4 * H_k * d + 2 * H_v * d + 8 * H_v)
+        self.group = layers_per_call(n_layers, H_v, need, copy_bytes, bound)
         rest = n_layers % self.group
         self.gdn_ws = torch.empty(max(need(self.group), need(rest) if rest else 0, 1), dtype=torch.uint8, device=dev)
         self.inputs = None
-        self._packed = self._input_buffers(torch.empty, self.group)
+        self._packed = self._input_buffers(torch.empty, self.group) if self.group > 1 else None
         self.indexed = indexed
         if indexed:
             self.slot = torch.zeros(self.capacity, dtype=torch.int32, device=dev)
@@ -187,9 +199,14 @@ class DeltaSStream:
             raise ValueError("score table full")
         # every launch and copy of the step on one stream (the caller's, else the current one)
         with _on(stream):
-            if self.group < self.L:   # a layer of a later group is refused before the first one runs
+            if self.group < self.L or self.L == 1:   # a layer of a later group is refused before the first one runs
                 check_layer_inputs(layer_inputs, T, self.H_k, self.H_v, self.d, self.state.get_device())
             for a in range(0, self.L, self.group):
+                if self.group == 1:   # as it is
+                    st = self.state[a]
+                    gdn_chunk_fwd(*layer_inputs[a], [T], 0, state_in=st, state_out=st, o=self.o[a, :T],
+                                  drift_partials=self.partials[a], workspace=self.gdn_ws, drift_per_slice=self.per_slice)
+                    continue
                 x = self._packed if self.L - a >= self.group else [t[:self.L - a] for t in self._packed]
                 gdn_pack_layers(layer_inputs if self.group == self.L else layer_inputs[a:a + self.group], T, x)
                 self._layers(T, a, x)

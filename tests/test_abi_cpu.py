@@ -325,3 +325,21 @@ def test_layers_fwd_refuses_what_its_kernels_would_misread(ds):
     go("another size", state=S[:1])
     go("same GPU")
     go("same GPU", o=o.to("meta"))
+
+
+def test_layers_per_call(ds):
+    """How a session groups its layers: within the bound, in calls of about equal size that fill the GPU the fewest times."""
+    from paper_2609_27470_amd.streaming import layers_per_call
+    per = lambda size: lambda n: n * size  # noqa: E731
+    assert layers_per_call(24, 32, per(3), 2, 1000) == 24          # all fit
+    assert layers_per_call(24, 32, per(28), 68, 1024) == 8         # 15 would fit: three calls of 256 heads, not two of 384
+    assert layers_per_call(24, 32, per(28), 1, 12 * 28) == 8
+    assert layers_per_call(24, 32, per(28), 1, 7 * 28) == 6        # four calls of 192 heads
+    assert layers_per_call(5, 4, per(10), 1, 49) == 3 and layers_per_call(5, 4, per(10), 1, 20) == 2
+    assert layers_per_call(5, 4, per(10), 1, 0) == 1 and layers_per_call(1, 64, per(10), 1, 0) == 1
+    assert layers_per_call(8, 32, lambda n: 0 if n > 3 else n, 1, 1000) == 3   # more than three are too large for one call
+    for L in range(1, 30):
+        for H_v in (1, 16, 32, 64, 300):
+            for most in range(1, L + 1):
+                n = layers_per_call(L, H_v, per(1), 0, most)
+                assert 1 <= n <= most

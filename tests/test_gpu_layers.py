@@ -195,10 +195,18 @@ def test_workspace_bound_of_a_session(ds):
     whole.step(xs, rows, rows)
     for bound, group in ((need(5), 5), (need(5) - 1, 3), (need(2), 2), (need(1), 1), (0, 1)):
         s = new(layers_workspace=bound)
-        assert s.group == group and s.gdn_ws.numel() <= max(bound, need(1)) and s._packed[0].shape[0] == group
+        assert s.group == group and s.gdn_ws.numel() <= max(bound, need(1))
+        assert s._packed is None if group == 1 else s._packed[0].shape[0] == group
+        t = new(layers_workspace=bound)
+        t.capture_graph()
+        for i, buf in enumerate(t.inputs):
+            for l in range(L):
+                buf[l, :T].copy_(xs[l][i])
         s.step(xs, rows, rows)
-        assert torch.equal(s.state, whole.state) and torch.equal(s.o[:, :T], whole.o[:, :T])
-        assert torch.equal(s.scores[:1], whole.scores[:1])
+        t.step_inputs(T, rows, rows)
+        for u in (s, t):
+            assert torch.equal(u.state, whole.state) and torch.equal(u.o[:, :T], whole.o[:, :T])
+            assert torch.equal(u.scores[:1], whole.scores[:1])
         s2 = new(layers_workspace=bound)
         with pytest.raises(ValueError):
             s2.step(xs[:4] + [xs[4][:3] + (xs[4][3][:, :1].expand(T, H_v),) + xs[4][4:]], rows, rows)
@@ -232,3 +240,28 @@ def test_frames_at_a_pitch(ds, L, T, pitch, H_k, H_v, d, frame_len, per_slice):
         assert rel(o[l, :T], r["o"]) <= 5e-5 and rel(S[l], r["state"][0]) <= 5e-5, l
         assert rel(p[l * F:(l + 1) * F], r["drift_partials"]) <= 1e-4, l
     assert bool((p[L * F:] == 0).all()) and bool((o[:, T:] == 5).all())
+
+
+@pytest.mark.parametrize("H_k,H_v,d,T", [(1, 2, 64, 40), (2, 4, 128, 130), (2, 4, 128, 90), (32, 64, 128, 70)])
+def test_session_of_one_layer(ds, H_k, H_v, d, T):
+    """A single layer's inputs are taken as they are: step holds no copy of them and gives step_inputs' bits, also for
+    tensors of more rows; what it refuses of several layers it refuses here."""
+    from paper_2609_27470_amd.streaming import DeltaSStream
+    new = lambda: DeltaSStream(1, H_k, H_v, d, 1, 64, 400, 140, 16, 4, 64, 2, device=DEV)  # noqa: E731
+    a, b = new(), new()
+    b.capture_graph()
+    assert a._packed is None
+    rows = torch.randint(-99, 99, (1, T, 64), dtype=torch.int16, device=DEV)
+    for c in range(3):
+        x = layers(1, T, H_k, H_v, d, seed=c)[0]
+        for buf, t in zip(b.inputs, x):
+            buf[0, :T].copy_(t)
+        longer = tuple(torch.cat([t, t]) for t in x)
+        a.step([x[:1] + longer[1:] if c == 1 else x], rows, rows)
+        b.step_inputs(T, rows, rows)
+        assert torch.equal(a.state, b.state) and torch.equal(a.o[:, :T], b.o[:, :T])
+        assert torch.equal(a.scores[:c + 1], b.scores[:c + 1])
+    for bad in (x[:2] + (x[2].half(),) + x[3:], x[:3] + (x[3][:, :1].expand(T, H_v),) + x[4:], x[:4] + (x[4].cpu(),), x[:4]):
+        with pytest.raises(ValueError):
+            a.step([bad], rows, rows)
+    assert a.n_chunks == 3 and torch.equal(a.state, b.state)
