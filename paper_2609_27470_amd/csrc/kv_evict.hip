@@ -218,23 +218,21 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
     __shared__ int s_keep[SEL_STEP];  // a copy of the keep list's first entries for the indexed variant's move
     __shared__ int s_scan[SEL_SUB * (SEL_THREADS / 64) + 1];
     __shared__ long long s_ll[SEL_THREADS / 64];
-    __shared__ int s_bad;
+    __shared__ int s_bad[SEL_THREADS / 64];  // per wave, written by it alone
     const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     if (tid == 0) {
         a.status[0] = 0;
         a.status[1] = 0;
         a.status[2] = 0;
-        s_bad = 0;
     }
     if (tid < a.n_planes) a.plane_tab[tid] = a.planes[tid];
-    lds_sync();  // s_bad is cleared before any wave can raise it
 
     const int c0 = a.n_s, c1 = a.len - a.n_w;
 
     // ---- pass 1: cache invariants and runs of equal chunk id among the
     // candidates [c0, c1)
-    int R = 0;
+    int R = 0, bad = 0;
     for (int base = 0; base < a.len; base += SEL_STEP) {
         int ch[SEL_SUB][SEL_PER], ps[SEL_SUB][SEL_PER], pc0[SEL_SUB], pp0[SEL_SUB], off[SEL_SUB];
 #pragma unroll
@@ -246,7 +244,6 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
             pc0[u] = has_prev ? a.chunk[lo - 1] : -1;
             pp0[u] = has_prev ? a.pos[lo - 1] : 0;
         }
-        int bad = 0;
         unsigned starts[SEL_SUB];  // the slots of the thread's four at which a run starts
 #pragma unroll
         for (int u = 0; u < SEL_SUB; ++u) {
@@ -276,7 +273,6 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
             }
             off[u] = __popc(starts[u]);
         }
-        if (bad) atomicOr(&s_bad, 1);
         int tot = 0;
         block_excl_scan(off, s_scan, tot);
 #pragma unroll
@@ -296,8 +292,13 @@ __global__ __launch_bounds__(SEL_THREADS) void kv_select_kernel(KvArgs a) {
         }
         R += tot;
     }
+    const bool wave_bad = __ballot(bad) != 0;
+    if ((tid & 63) == 0) s_bad[wid] = wave_bad;
     __syncthreads();
-    if (s_bad) {
+    int any_bad = 0;
+#pragma unroll
+    for (int w = 0; w < SEL_THREADS / 64; ++w) any_bad |= s_bad[w];
+    if (any_bad) {
         if (tid == 0) {
             a.status[0] = 1;
             a.status[1] = 1;
